@@ -134,6 +134,14 @@ __device__ __forceinline__ int opaque(int x) {
 // wait until this wave's memory operations (stores included) have completed
 __device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
+// barrier of a work-group whose waves fill LDS with LDS-direct loads: all but this wave's newest N
+// vector memory operations have completed (LDS-direct loads complete when their data is in LDS),
+// and so have its LDS reads, before it arrives.  No wait for the N newest, unlike __syncthreads.
+template <int N>
+__device__ __forceinline__ void wait_vm_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
 // ---- temperature sampling: Gumbel-max draws ----
 // Philox4x64-10 (Salmon, Moraes, Dror, Shaw, "Parallel random numbers: as easy as 1, 2, 3",
 // SC 2011) of the counter (c0, c1, c2, c3) under the key (k0, k1); the four output words

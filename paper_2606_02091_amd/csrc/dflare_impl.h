@@ -173,6 +173,7 @@ struct KvtArgs {
   int Lcap, hd, kv_tiles;
   const float2* rope;
   const float* bias;       // optional fp32 [D][K kv | V kv], added before the rotation
+  int kparts;              // pieces of the K range, each summed from zero (set by launch_kvt)
 };
 
 // ---- launchers (kernels.hip) ----
@@ -194,7 +195,7 @@ void launch_accept(hipStream_t s, const int32_t* block_ids, const int32_t* draft
 void launch_fused_rows(hipStream_t s, const u32x4* ua_hi, const u32x4* ua_lo, const float* ustats, int n,
                        int H, int D, int n_max, int mt_max, float eps, float* out);
 bool kvt_shape_supported(int nt_per_block, int waves);
-void launch_kvt(hipStream_t s, int nt_per_block, int waves, const KvtArgs& a, int layers, int mtiles);
+void launch_kvt(hipStream_t s, int cus, int nt_per_block, int waves, KvtArgs a, int layers, int mtiles);
 // Phases [p0, p1) of a draft block on `blocks` work-groups of kThreads threads, which wait at
 // grid barriers between phases (p1 > p0 + 1 needs all of them resident: one per CU, placed
 // at once when no other stream holds CUs).  cooperative = true asks the runtime to

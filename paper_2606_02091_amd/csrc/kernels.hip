@@ -152,6 +152,43 @@ __global__ void k_fused_rows(const u32x4* ua_hi, const u32x4* ua_lo, const float
   }
 }
 
+// Epilogue of a 16 x 16 result tile (output tile nt, row tile mt) of the context K/V projection:
+// bias, rotation of K and the fp16 stores into cache slots L + row.  v holds the lane's column of
+// rows 4 quad .. 4 quad + 3, already scaled by 1 / rms.
+__device__ __forceinline__ void kvt_store(const KvtArgs& a, int layer, int nt, int mt, f32x4 v, int lane) {
+  const int quad = lane >> 4, col = lane & 15;
+  const int tph = a.hd / 16, half = a.hd / 2;
+  const int L0 = a.Lp ? *a.Lp : a.L;  // rows go to cache slots L0 + row
+  uint16_t* kc = a.kc + layer * a.cache_layer_stride;
+  uint16_t* vt = a.vt + layer * a.cache_layer_stride;
+  const bool is_k = nt < a.kv_tiles;
+  const int t = is_k ? nt : nt - a.kv_tiles;
+  const int head = t / tph, jj = t % tph;
+  // bias of this lane's column (K columns are packed in rotary pair order)
+  const int kvd = a.kv_tiles * 16;
+  const int kdim = (col < 8) ? 8 * jj + (col & 7) : half + 8 * jj + (col & 7);
+  const float bcol =
+      a.bias ? a.bias[(long)layer * 2 * kvd + (is_k ? head * a.hd + kdim : kvd + head * a.hd + jj * 16 + col)] : 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = mt * 16 + quad * 4 + i;
+    const bool valid = row < a.n_new;
+    const int slot = L0 + row;
+    const float x = v[i] + bcol;
+    const float partner = __shfl_xor(x, 8);
+    if (is_k) {
+      const int m = 8 * jj + (col & 7);
+      const int dim = (col < 8) ? m : half + m;
+      const float2 cs = a.rope[(long)(valid ? slot : 0) * half + m];
+      const float y = (col < 8) ? (x * cs.x - partner * cs.y) : (x * cs.x + partner * cs.y);
+      if (valid) kc[((long)head * a.Lcap + slot) * a.hd + dim] = f2h(y);
+    } else if (valid) {
+      const int dim = jj * 16 + col;
+      vt[((long)head * a.hd + dim) * a.Lcap + slot] = f2h(x);
+    }
+  }
+}
+
 // ------------------------------------------------------------------------------------------
 // context K/V projection of fuse_append (Eq. 4, W^t): RoPE(f W_K^t) and f W_V^t for every
 // appended row of every draft layer, into cache slots L + row.  Weight-streaming GEMM:
@@ -276,36 +313,158 @@ __global__ __launch_bounds__(64 * WAVES) void k_kvt(KvtArgs a) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) v[i] *= s_rstd[quad * 4 + i];
 
-  if (has_tile) {
-    const int tph = a.hd / 16, half = a.hd / 2;
-    const int L0 = a.Lp ? *a.Lp : a.L;  // rows go to cache slots L0 + row
-    uint16_t* kc = a.kc + layer * a.cache_layer_stride;
-    uint16_t* vt = a.vt + layer * a.cache_layer_stride;
-    const bool is_k = nt < a.kv_tiles;
-    const int t = is_k ? nt : nt - a.kv_tiles;
-    const int head = t / tph, jj = t % tph;
-    // bias of this lane's column (K columns are packed in rotary pair order)
-    const int kvd = a.kv_tiles * 16;
-    const int kdim = (col < 8) ? 8 * jj + (col & 7) : half + 8 * jj + (col & 7);
-    const float bcol =
-        a.bias ? a.bias[(long)layer * 2 * kvd + (is_k ? head * a.hd + kdim : kvd + head * a.hd + jj * 16 + col)] : 0.f;
+  if (has_tile) kvt_store(a, layer, nt, mt, v, lane);
+}
+
+// The same projection for appends of many rows (prompt ingestion).  k_kvt streams the whole
+// weight matrix once per 16 rows; here a work-group of 4 waves (WM x WN) owns WM MT row tiles x
+// WN NT output tiles, and each k-tile's fragments (both A planes and the weights) go through a
+// three-stage LDS ring filled by LDS-direct loads two k-tiles ahead, one barrier per k-tile.
+// The K range is cut into the same a.kparts pieces that k_kvt's waves take, each accumulated
+// from zero and added in order, so that every row's result is the one k_kvt gives bit for bit,
+// however many rows an append holds.  Bound by the barrier and LDS latency of a k-tile (two
+// waves per SIMD: 37 cycles per MFMA at the 128 x 128 tile, 16 is the least) and, for few rows,
+// by the weight stream.  512 rows, 8 layers: 88 us at H = 2,560 and 8 heads x 128 (978 TFLOP/s
+// on both planes; k_kvt 638), 124 at H = 4,096 (892), 58 at H = 2,880 and 8 x 64 (347).
+template <int MT, int NT, int WM, int WN, int NS>
+__global__ __launch_bounds__(256, 2) void k_kvt_rows(KvtArgs a) {
+  constexpr int BM = MT * WM, BN = NT * WN, NF = 2 * BM + BN, PER = NF / 4;
+  static_assert(WM * WN == 4 && NF % 4 == 0, "4 waves share the loads evenly");
+  // one LDS array: with two, the compiler's alias information makes it wait for every LDS-direct
+  // load in flight before each LDS read
+  __shared__ u32x4 st[NS * NF * 64 + BM * 4];
+  float* s_rstd = reinterpret_cast<float*>(st + NS * NF * 64);
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = w / WN, wn = w % WN;
+  const int Mt = (a.n_new + 15) / 16;
+  const int Mg = (Mt + BM - 1) / BM, Ng = (a.Nt + BN - 1) / BN;
+  // work-groups go to the 8 XCDs in turn: each XCD takes a contiguous range of (layer, output
+  // tiles, rows), so that its work-groups share a layer's rows and weights in its L2
+  const int nb = gridDim.x, bid = blockIdx.x;
+  const int t0 = (nb % 8 == 0) ? (bid % 8) * (nb / 8) + bid / 8 : bid;
+  const int mg = t0 % Mg, ng = (t0 / Mg) % Ng, layer = t0 / (Mg * Ng);
+
+  // this wave's PER fragments of a stage: 0 .. BM-1 A hi, BM .. 2 BM-1 A lo, then the weights;
+  // tiles past the rows or the output come from the zero tile
+  const u32x4* src[PER];
+  int step[PER];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = mt * 16 + quad * 4 + i;
-      const bool valid = row < M;
-      const int slot = L0 + row;
-      const float x = v[i] + bcol;
-      const float partner = __shfl_xor(x, 8);
-      if (is_k) {
-        const int m = 8 * jj + (col & 7);
-        const int dim = (col < 8) ? m : half + m;
-        const float2 cs = a.rope[(long)(valid ? slot : 0) * half + m];
-        const float y = (col < 8) ? (x * cs.x - partner * cs.y) : (x * cs.x + partner * cs.y);
-        if (valid) kc[((long)head * a.Lcap + slot) * a.hd + dim] = f2h(y);
-      } else if (valid) {
-        const int dim = jj * 16 + col;
-        vt[((long)head * a.hd + dim) * a.Lcap + slot] = f2h(x);
+  for (int i = 0; i < PER; ++i) {
+    const int f = w * PER + i;
+    const u32x4* p;
+    bool ok;
+    if (f < 2 * BM) {
+      const int mt = mg * BM + (f < BM ? f : f - BM);
+      ok = mt < Mt;
+      p = (f < BM ? a.Ahi : a.Alo) + layer * a.a_layer_stride + (long)mt * a.Kt * 64;
+    } else {
+      const int nt = ng * BN + f - 2 * BM;
+      ok = nt < a.Nt;
+      p = a.W + layer * a.w_layer_stride + (long)nt * a.Kt * 64;
+    }
+    src[i] = (ok ? p : a.zero) + lane;
+    step[i] = ok ? 64 : 0;
+  }
+  auto issue = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const u32x4* s = src[i];
+      __builtin_amdgcn_global_load_lds(s, (LDSP char*)(char*)&st[(buf * NF + w * PER + i) * 64], 16, 0, 0);
+      src[i] += step[i];
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < NS - 1; ++i)
+    if (i < a.Kt) issue(i);
+
+  // 1/rms of the fused rows (Eq. 3), summed as k_kvt sums it: 16 threads per row, each thread
+  // its part of BM rows at once, four values of each in flight
+  {
+    const int part = tid & 15, g0 = mg * BM * 16 + (tid >> 4);
+    const float* sp = a.stats + layer * a.stats_layer_stride;
+    float s[BM];
+#pragma unroll
+    for (int i = 0; i < BM; ++i) s[i] = 0.f;
+    for (int q0 = part; q0 < a.n_stat; q0 += 64) {
+      float x[BM][4];
+#pragma unroll
+      for (int i = 0; i < BM; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int row = min(g0 + 16 * i, a.n_new - 1), q = q0 + 16 * e;
+          x[i][e] = sp[(long)row * a.n_stat + min(q, a.n_stat - 1)];
+          if (q >= a.n_stat) x[i][e] = 0.f;  // s + 0 is s
+        }
+#pragma unroll
+      for (int i = 0; i < BM; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[i] += x[i][e];
+    }
+#pragma unroll
+    for (int i = 0; i < BM; ++i) {
+      s[i] += __shfl_xor(s[i], 8);
+      s[i] += __shfl_xor(s[i], 4);
+      s[i] += __shfl_xor(s[i], 2);
+      s[i] += __shfl_xor(s[i], 1);
+      if (part == 0) s_rstd[(tid >> 4) + 16 * i] = g0 + 16 * i < a.n_new ? rsqrtf(s[i] * a.inv_dim + a.eps) : 0.f;
+    }
+  }
+
+  f32x4 v[MT][NT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int n = 0; n < NT; ++n) v[m][n] = f32x4{-0.f, -0.f, -0.f, -0.f};  // -0 + x is x for every x
+  const char* L0 = reinterpret_cast<const char*>(&st[0]) + lane * 16;
+  int kt = 0, buf = 0;
+  for (int part = 0; part < a.kparts; ++part) {
+    const int end = (a.Kt * (part + 1)) / a.kparts;
+    f32x4 ah[MT][NT], al[MT][NT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int n = 0; n < NT; ++n) ah[m][n] = al[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (; kt < end; ++kt) {
+      // this wave's loads of k-tile kt have landed (those of kt + 1 may be in flight), then
+      // everybody's; every wave is past its reads of k-tile kt - 1, whose buffer is refilled
+      if (kt + NS - 2 < a.Kt) wait_vm_barrier<(NS - 2) * PER>();
+      else wait_vm_barrier<0>();
+      if (kt + NS - 1 < a.Kt) issue(buf == 0 ? NS - 1 : buf - 1);
+      const char* L = L0 + buf * (NF * 1024);
+      u32x4 wf[NT];
+#pragma unroll
+      for (int n = 0; n < NT; ++n) wf[n] = *reinterpret_cast<const u32x4*>(L + (2 * BM + wn * NT + n) * 1024);
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        const u32x4 xh = *reinterpret_cast<const u32x4*>(L + (wm * MT + m) * 1024);
+        const u32x4 xl = *reinterpret_cast<const u32x4*>(L + (BM + wm * MT + m) * 1024);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+          ah[m][n] = mfma(xh, wf[n], ah[m][n]);
+          al[m][n] = mfma(xl, wf[n], al[m][n]);
+        }
       }
+      buf = buf == NS - 1 ? 0 : buf + 1;
+    }
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int n = 0; n < NT; ++n) v[m][n] += ah[m][n] + al[m][n];
+  }
+  __syncthreads();  // s_rstd (with one k-tile or none no barrier of the loop has covered it)
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const int mt = mg * BM + wm * MT + m;
+    if (mt >= Mt) continue;
+    const f32x4 r = *reinterpret_cast<const f32x4*>(s_rstd + (wm * MT + m) * 16 + (lane >> 4) * 4);
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int nt = ng * BN + wn * NT + n;
+      if (nt >= a.Nt) continue;
+      f32x4 x = v[m][n];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] *= r[i];
+      kvt_store(a, layer, nt, mt, x, lane);
     }
   }
 }
@@ -1741,7 +1900,30 @@ bool kvt_shape_supported(int nt_per_block, int waves) {
   return (nt_per_block == 1 && waves == 16) || (nt_per_block == 2 && waves == 8);
 }
 
-void launch_kvt(hipStream_t s, int nt_per_block, int waves, const KvtArgs& a, int layers, int mtiles) {
+template <int MT, int NT, int WM, int WN, int NS>
+static void launch_kvt_rows(hipStream_t s, const KvtArgs& a, int layers, int mtiles) {
+  const int Mg = (mtiles + MT * WM - 1) / (MT * WM), Ng = (a.Nt + NT * WN - 1) / (NT * WN);
+  hipLaunchKernelGGL((k_kvt_rows<MT, NT, WM, WN, NS>), dim3(Mg * Ng * layers), dim3(256), 0, s, a);
+}
+
+// Appends of up to 16 rows stream the weights through k_kvt (H = 2,560: 25 us, 26 with the
+// smallest tile of k_kvt_rows; H = 4,096: 35 and 36).  More rows take the smallest tile whose
+// work-groups all run at once, two per CU, else the largest: a larger tile re-reads less but runs
+// longer with idle CUs, and one more round of the smaller costs its whole length again
+// (H = 4,096, 32 x 64 / 32 x 128 / 64 x 128 / 128 x 128: 64 rows 39 / 43 / 61 / 95 us, 128 rows
+// 71 / 48 / 62 / 96, 256 rows 121 / 102 / 74 / 97, 512 rows 251 / 208 / 144 / 124).
+void launch_kvt(hipStream_t s, int cus, int nt_per_block, int waves, KvtArgs a, int layers, int mtiles) {
+  a.kparts = waves;
+  if (mtiles > 1) {
+    auto fits = [&](int rows, int cols) {
+      return (long)((mtiles + rows - 1) / rows) * ((a.Nt + cols - 1) / cols) * layers <= 2L * cus;
+    };
+    if (fits(2, 4)) launch_kvt_rows<2, 1, 1, 4, 6>(s, a, layers, mtiles);
+    else if (fits(2, 8)) launch_kvt_rows<2, 2, 1, 4, 6>(s, a, layers, mtiles);
+    else if (fits(4, 8)) launch_kvt_rows<4, 2, 1, 4, 4>(s, a, layers, mtiles);
+    else launch_kvt_rows<4, 4, 2, 2, 3>(s, a, layers, mtiles);
+    return;
+  }
   const dim3 grid((a.Nt + nt_per_block - 1) / nt_per_block, layers, mtiles);
   if (nt_per_block == 2 && waves == 8) hipLaunchKernelGGL((k_kvt<2, 8>), grid, dim3(512), 0, s, a);
   else hipLaunchKernelGGL((k_kvt<1, 16>), grid, dim3(1024), 0, s, a);

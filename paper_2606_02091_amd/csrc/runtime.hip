@@ -1230,7 +1230,7 @@ int append_rows(dflare_handle* h, const void* target_hidden, int32_t n_new, int 
   a.rope = h->rope;
   a.bias = h->kv_bias;
   prof_mark(h, DFLARE_K_KV_T, true);
-  launch_kvt(s, h->kvt_nt, h->kvt_waves, a, D, ceil_div(n_new, 16));
+  launch_kvt(s, h->cus, h->kvt_nt, h->kvt_waves, a, D, ceil_div(n_new, 16));
   prof_mark(h, DFLARE_K_KV_T, false);
   if (h->debug) {
     launch_fused_rows(s, h->ua_hi, h->ua_lo, h->Ustats, n_new, H, D, c.max_new, h->mt_max, c.rms_eps,

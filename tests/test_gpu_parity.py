@@ -179,6 +179,36 @@ def test_incremental_append_is_bitwise_bulk():
     inc.close()
 
 
+# one append against appends of at most 16 rows, bit for bit: the many-row kernels at the edges of
+# their tiles (32, 64 and 128 rows; which tile runs follows from rows x heads x layers), ragged
+# rows, K ranges with fewer k-tiles than the K pieces (H = 96: three), a width that is no
+# multiple of the fusion's 512 columns, more layers than the fused kernel takes
+@pytest.mark.parametrize("hidden,n_kv,hd,layers", [(96, 8, 128, 8), (544, 16, 64, 8), (160, 3, 64, 9)])
+def test_many_row_append_is_bitwise_small_appends(hidden, n_kv, hd, layers):
+    cfg = synth.ModelConfig("rows", hidden=hidden, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd, ffn=64, vocab=64,
+                            n_draft_layers=layers, n_target_layers=7, block_size=4, context=520)
+    w, lg = P.weights_for(cfg)
+    rows = synth.hidden_rows(cfg, 0, 520)
+    ref = dfl.DraftModel(cfg, w, lg, max_context=520, max_new=16)
+    for s in range(0, 520, 13):
+        ref.fuse_append(dev(np.ascontiguousarray(rows[:, s:s + 13])))
+
+    def caches(m, n):
+        return [dfl.dflare_debug_read(m.h, what, i, (m.context_len, n_kv, hd))[:n] for i in range(layers)
+                for what in (dfl.DBG_KCACHE, dfl.DBG_VCACHE)]
+
+    want = caches(ref, 520)
+    bulk = dfl.DraftModel(cfg, w, lg, max_context=520, max_new=520)
+    for n in (17, 32, 33, 64, 65, 127, 128, 129, 257, 385, 520):
+        print(f"[append] H={hidden} n_kv={n_kv} hd={hd} D={layers}: {n} rows", flush=True)
+        bulk.truncate(0)
+        bulk.fuse_append(dev(np.ascontiguousarray(rows[:, :n])))
+        for a, b in zip(caches(bulk, n), want):
+            assert np.array_equal(a, b[:n]), n
+    ref.close()
+    bulk.close()
+
+
 def test_repeat_is_deterministic_and_cache_untouched():
     cfg = CASES["gqa8_hd64"][0]
     model, orc, _, _ = build_pair(cfg, 300, "random")
