@@ -132,6 +132,87 @@ __global__ __launch_bounds__(64) void k_fuse(const uint16_t* __restrict__ hidden
   }
 }
 
+// The same fusion for appends of many rows and D <= kFuseMaxD layers: a wave takes 512 columns of
+// one row for all D layers, so the target rows are read once instead of D times (from L2 at best).
+// Every sum is formed in k_fuse's order, so a row's result does not depend on which kernel ran.
+// Bound by memory: the rows once and the fragments once.  The 16 rows of a tile run on one XCD,
+// whose L2 then fills whole lines of the fragments (16 bytes of a line per row): spread over the
+// XCDs, 512 rows took 51 us at H = 2,560, S = 18 and 60 at H = 2,880, S = 24, and here 37 and 39;
+// k_fuse takes 60 and 73 (H = 4,096, S = 36: 80 against 125).  With few rows its D-fold
+// parallelism wins (16 rows: 10 against 19 us); the two meet at 128 rows for all three shapes.
+constexpr int kFuseMaxD = 8;
+constexpr int kFuseLayersRows = 128;  // rows of an append from which k_fuse_layers runs
+__global__ __launch_bounds__(64) void k_fuse_layers(const uint16_t* __restrict__ hidden, int ld, int S, int H, int n, int D,
+                                                    const float* __restrict__ alpha, const float* __restrict__ gain,
+                                                    float* ustats, u32x4* ua_hi, u32x4* ua_lo, int n_max, int mt_max) {
+  constexpr int JB = 6;  // target rows per batch, the next batch in flight
+  const int lane = threadIdx.x;
+  const int cbs = (H + 511) / 512;
+  // block id b = x + 8 (row of the tile + 16 (p / 8)): pair p = (16-row tile, 512 columns) with p % 8 = x
+  const int b = blockIdx.x, p = kXcds * (b / (kXcds * 16)) + b % kXcds;
+  const int r = (p / cbs) * 16 + (b / kXcds) % 16, cb = p % cbs;
+  if (r >= n) return;
+  const int k0 = cb * 512 + lane * 8;
+  const bool ok = k0 < H;
+  const int Kt = H / 32;
+  const uint16_t* src = hidden + (long)r * H + (ok ? k0 : 0);
+  float u[kFuseMaxD][8];
+#pragma unroll
+  for (int i = 0; i < kFuseMaxD; ++i)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) u[i][e] = 0.f;
+  auto fetch = [&](int j0, u32x4* v) {
+#pragma unroll
+    for (int jj = 0; jj < JB; ++jj)
+      v[jj] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + (long)min(j0 + jj, S - 1) * ld * H));
+  };
+  auto add = [&](int j0, const u32x4* v) {
+#pragma unroll
+    for (int jj = 0; jj < JB; ++jj) {
+      if (j0 + jj < S) {
+#pragma unroll
+        for (int i = 0; i < kFuseMaxD; ++i) {
+          if (i < D) {
+            const float a = alpha[i * S + j0 + jj];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              u[i][2 * e] = fmaf(a, bf2f(v[jj][e] & 0xFFFFu), u[i][2 * e]);
+              u[i][2 * e + 1] = fmaf(a, bf2f(v[jj][e] >> 16), u[i][2 * e + 1]);
+            }
+          }
+        }
+      }
+    }
+  };
+  u32x4 va[JB], vb[JB];
+  fetch(0, va);
+  for (int j0 = 0; j0 < S; j0 += 2 * JB) {
+    fetch(j0 + JB, vb);
+    add(j0, va);
+    fetch(j0 + 2 * JB, va);
+    add(j0 + JB, vb);
+  }
+#pragma unroll
+  for (int i = 0; i < kFuseMaxD; ++i) {
+    if (i >= D) break;
+    float sq = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sq += u[i][e] * u[i][e];
+    sq += __shfl_xor(sq, 1);
+    if (ok) {
+      float y[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] = u[i][e] * gain[(long)i * H + k0 + e];
+      u32x4 hi, lo;
+      split_pack8(y, hi, lo);
+      const long fo = ((long)i * mt_max * Kt * 64 * 8 + frag_off(r, k0, Kt)) >> 3;
+      ua_hi[fo] = hi;
+      ua_lo[fo] = lo;
+      if ((lane & 1) == 0) ustats[((long)i * n_max + r) * (H / 16) + k0 / 16] = sq;
+    }
+  }
+}
+
 // debug: materialise f^(i) = (hi + lo) * rstd, [D, n, H] fp32 (the gain is already applied)
 __global__ void k_fused_rows(const u32x4* ua_hi, const u32x4* ua_lo, const float* ustats, int n, int H, int D,
                              int n_max, int mt_max, float eps, float* out) {
@@ -1854,6 +1935,12 @@ void launch_bf16_to_f32(hipStream_t s, float* dst, const uint16_t* src, long n) 
 void launch_fuse(hipStream_t s, const uint16_t* hidden, int n, int ld, int S, int H, int D, const float* alpha,
                  const float* gain, float* ustats, u32x4* ua_hi, u32x4* ua_lo, int n_max, int mt_max) {
   const int pairs = ((H + 511) / 512) * n;
+  if (n >= kFuseLayersRows && D <= kFuseMaxD) {
+    const int tiles = ((n + 15) / 16) * ((H + 511) / 512);
+    hipLaunchKernelGGL(k_fuse_layers, dim3((tiles + kXcds - 1) / kXcds * kXcds * 16), dim3(64), 0, s, hidden, ld, S,
+                       H, n, D, alpha, gain, ustats, ua_hi, ua_lo, n_max, mt_max);
+    return;
+  }
   const int groups = (pairs + kXcds - 1) / kXcds;
   hipLaunchKernelGGL(k_fuse, dim3(groups * kXcds * D), dim3(64), 0, s, hidden, ld, S, H, n, D, alpha, gain, ustats,
                      ua_hi, ua_lo, n_max, mt_max);
