@@ -43,7 +43,7 @@ struct BGemmArgs {
   const u32x4* W;
   long w_layer;
   int Nt, Kt, Mt, M, kg, layers;
-  int nw;              // n-tiles per wave: kBNW, or 3 where that fills the CUs better
+  int nw;              // n-tiles per wave: kBNW, or 3 where that fills the CUs better (few rows: per work-group)
   const u32x4* zero;   // one zero fragment
   float* part;         // partial tiles [tiles][kg][kBPartFloats]
   unsigned* cnt;       // arrival counters [tiles], 32 words apart, zero between launches
@@ -73,7 +73,7 @@ struct BGemmArgs {
   int V;
   float* pmax;
   int* pidx;
-  int pld;
+  int pld, n_groups;   // rows per n-group in pmax and pidx, n-groups
   float inv_temp;
   unsigned draw;
   unsigned long long seed;
@@ -94,9 +94,15 @@ int bgemm_groups(int Nt, int Mt, int nw = kBNW);  // output tiles of one layer
 // n 16-byte slots of packed bf16 weight tiles -> fp16 (same layout)
 void launch_tiles_to_f16(hipStream_t s, u32x4* dst, const u32x4* src, long n);
 void launch_bgemm(hipStream_t s, int epi, const BGemmArgs& g, const BRows& rows);
+// the same for calls of at most kBStreamMt row tiles (QKV, RESID, SWIGLU and ARGMAX; g.nw output tiles per
+// work-group; RESID leaves its kg K parts in g.part, [kg][Mt * 16][H])
+constexpr int kBStreamMt = 8;
+void launch_bstream(hipStream_t s, int epi, const BGemmArgs& g, const BRows& rows);
 void launch_bargmax(hipStream_t s, const float* pmax, const int* pidx, int ngroups, int pld, int M, int* tokens);
 // RMSNorm of rows of X (or of embedding rows) into fp16 A fragments
-void launch_bnorm(hipStream_t s, const float* X, int M, int H, const float* gain, float eps, u32x4* A, int a_kt);
+// (kg > 0: the kg K parts [kg][ld_rows][H] of the projection before it are added to X first)
+void launch_bnorm(hipStream_t s, float* X, int M, int H, const float* part, int kg, long ld_rows, const float* gain,
+                  float eps, u32x4* A, int a_kt);
 void launch_bembed_norm(hipStream_t s, const uint16_t* embed, const int32_t* ids, int M, int H, int V,
                         const float* gain, float eps, float* X, u32x4* A, int a_kt);
 // layer fusion (Eq. 3) of N appended rows for every draft layer, normalised, into fp16 A

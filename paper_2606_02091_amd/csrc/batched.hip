@@ -492,6 +492,200 @@ __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(kBWavesPerS
   }
 }
 
+// ------------------------------------------------------------------------------------------
+// GEMM of few rows (M <= 16 MT).  The weights are streamed once and there is little to multiply
+// per weight, so nothing goes through LDS on the way in: a work-group of 4 waves owns TN output
+// tiles for all rows, its waves take a quarter of the K part each, and a wave loads its weight
+// and A fragments straight into registers, NS k-tiles in flight, with no barrier until the end.
+// Then the waves' sums meet in LDS in wave order and tile q goes to wave q % 4 for the epilogue.
+// RESID leaves its sums as K part kz of g.part ([kg][Mt * 16][H], row-major); k_bnorm adds the
+// parts to the residual stream.  Bound by the weight stream, and by A, which every work-group reads
+// whole from L2: gate/up at H = 4,096 and F = 12,288 takes 39 us of streaming at 16 rows (5.1 TB/s),
+// 49 at 64.  Event-timed against k_bgemm at 64 rows: Q/K/V 48 -> 24 us, output 35 -> 17, gate/up
+// 65 -> 54, down 51 -> 31, LM head of 151,936 447 -> 264; its 128-row tiles computed mostly padding
+// and passed whole fp32 tiles between the K parts.
+// ------------------------------------------------------------------------------------------
+template <int EPI, int MT, int TN, int NS>
+__global__ __launch_bounds__(256, 2) void k_bstream(BGemmArgs g, BRows rows) {
+  constexpr int NQ = MT * TN;           // output tiles of the work-group
+  constexpr int QW = (NQ + 3) / 4;      // of them finished by one wave
+  __shared__ f32x4 red[4][NQ][64];
+  __shared__ int s_slot[MT * 16];
+  __shared__ int s_pos[MT * 16];
+  __shared__ long s_cache[MT * 16];
+  __shared__ float s_bv[TN][MT * 16];
+  __shared__ int s_bi[TN][MT * 16];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int quad = lane >> 4, col = lane & 15;
+  const int Ng = (g.Nt + TN - 1) / TN;
+  const int ng = blockIdx.x % Ng, kz = (blockIdx.x / Ng) % g.kg, layer = blockIdx.x / (Ng * g.kg);
+  const int parts = 4 * g.kg, part = 4 * kz + w;
+  const int kb = (int)((long)part * g.Kt / parts), ke = (int)((long)(part + 1) * g.Kt / parts);
+  const int nk = ke - kb, klast = max(nk - 1, 0);
+  const int nt0 = ng * TN;
+
+  const u32x4* wp[TN];
+#pragma unroll
+  for (int n = 0; n < TN; ++n) wp[n] = g.W + layer * g.w_layer + ((long)min(nt0 + n, g.Nt - 1) * g.Kt + kb) * 64;
+  const u32x4* ap[MT];
+  int astep[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const bool ok = m < g.Mt;
+    ap[m] = ok ? g.A + layer * g.a_layer + ((long)m * g.Kt + kb) * 64 : g.zero;
+    astep[m] = ok ? 64 : 0;
+  }
+  f32x4 acc[MT][TN];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int n = 0; n < TN; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  u32x4 wr[NS][TN], ar[NS][MT];
+  // loads are never skipped (past the last k-tile they repeat it), so that the waits stay exact
+  auto load = [&](int i, int j) {
+    const int kt = min(i, klast);
+#pragma unroll
+    for (int n = 0; n < TN; ++n) wr[j][n] = __builtin_nontemporal_load(wp[n] + (long)kt * 64 + lane);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) ar[j][m] = ap[m][(long)kt * astep[m] + lane];
+  };
+  if (nk > 0) {
+#pragma unroll
+    for (int j = 0; j < NS; ++j) load(j, j);
+    for (int t0 = 0; t0 < nk; t0 += NS) {
+#pragma unroll
+      for (int j = 0; j < NS; ++j) {
+        if (t0 + j < nk) {
+#pragma unroll
+          for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int n = 0; n < TN; ++n) acc[m][n] = mfma_h(ar[j][m], wr[j][n], acc[m][n]);
+        }
+        load(t0 + j + NS, j);
+      }
+    }
+  }
+  if constexpr (EPI == BEPI_QKV || EPI == BEPI_ARGMAX) {
+    if (tid < MT * 16) {
+      const int row = min(tid, g.M - 1);
+      int i = 0;
+      while (i + 1 < rows.n_seq && row >= rows.off[i + 1]) ++i;
+      s_pos[tid] = row - rows.off[i];
+      s_slot[tid] = EPI == BEPI_QKV ? rows.L[i] + (row - rows.off[i]) : rows.seq[i];
+      s_cache[tid] = (long)rows.seq[i] * g.seq_stride + (long)(g.layer0 + layer) * g.cache_layer;
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int n = 0; n < TN; ++n) red[w][n * MT + m][lane] = acc[m][n];
+  __syncthreads();
+
+#pragma unroll
+  for (int qi = 0; qi < QW; ++qi) {
+    const int q = qi * 4 + w, n = q / MT, m = q % MT;
+    const int nt = nt0 + n;
+    if (q >= NQ || nt >= g.Nt || m >= g.Mt) continue;
+    f32x4 v = red[0][q][lane];
+    v += red[1][q][lane];
+    v += red[2][q][lane];
+    v += red[3][q][lane];
+    const int r0 = m * 16 + quad * 4;  // the lane's rows r0 .. r0 + 3, column nt * 16 + col
+    if constexpr (EPI == BEPI_RESID) {
+      float* dst = g.part + ((long)kz * g.Mt * 16 + r0) * g.H + nt * 16 + col;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dst[(long)e * g.H] = v[e];
+    } else if constexpr (EPI == BEPI_SWIGLU) {
+      uint32_t* out = reinterpret_cast<uint32_t*>(g.out16);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float gt = v[e];
+        const float up = __shfl_xor(gt, 8);
+        const float hv = (col < 8) ? gt / (1.0f + expf(-gt)) * up : 0.f;
+        const float h1 = __shfl_xor(hv, 1);
+        if (r0 + e < g.M && col < 8 && (col & 1) == 0)
+          out[frag_off(r0 + e, nt * 8 + col, g.out_kt) >> 1] = pack_h2(hv, h1);
+      }
+    } else if constexpr (EPI == BEPI_QKV) {
+      const int tph = g.hd / 16, half = g.hd / 2, kvd = g.kv_tiles * 16;
+      const int region = nt < g.q_tiles ? 0 : nt < g.q_tiles + g.kv_tiles ? 1 : 2;  // Q, K, V
+      const int tt = region == 0 ? nt : region == 1 ? nt - g.q_tiles : nt - g.q_tiles - g.kv_tiles;
+      const int head = tt / tph, jj = tt % tph;
+      const int mm = 8 * jj + (col & 7), dim = (col < 8) ? mm : half + mm;
+      const float* kvb = g.bias ? g.bias + (long)(g.layer0 + layer) * 2 * kvd : nullptr;
+      const float bcol =
+          (kvb && region > 0) ? kvb[(region == 1 ? 0 : kvd) + head * g.hd + (region == 1 ? dim : jj * 16 + col)] : 0.f;
+      float2 cs[4];
+      if (region < 2) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cs[e] = g.rope[(long)s_slot[r0 + e] * half + mm];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = r0 + e, slot = s_slot[r];
+        const float x = v[e] + bcol;
+        const float partner = __shfl_xor(x, 8);
+        if (region < 2) {
+          const float y = (col < 8) ? (x * cs[e].x - partner * cs[e].y) : (x * cs[e].x + partner * cs[e].y);
+          if (region == 0) g.Q[(long)r * g.q_dim + head * g.hd + dim] = y;  // rows past M: padding rows of Q
+          else if (r < g.M) g.kc[s_cache[r] + ((long)head * g.Lcap + slot) * g.hd + dim] = f2h(y);
+        } else if (r < g.M) {
+          g.vt[s_cache[r] + ((long)head * g.hd + jj * 16 + col) * g.Lcap + slot] = f2h(x);
+        }
+      }
+    } else {
+      const int vc = nt * 16 + col;
+      float z[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (vc < g.V && r0 + e < g.M && g.logits) g.logits[(long)(r0 + e) * g.V + vc] = v[e];
+        z[e] = v[e];
+      }
+      if (g.inv_temp > 0.f) {
+        // rows 4 q .. 4 q + 3 of one sequence share one Philox call, else one call per row
+        const bool grouped = (s_pos[r0] & 3) == 0 && s_pos[r0 + 3] == s_pos[r0] + 3 && s_slot[r0 + 3] == s_slot[r0];
+        uint64_t words[4];
+#pragma unroll 1
+        for (int e = 0; e < 4; ++e) {
+          const int pos = s_pos[r0 + e];
+          if (e == 0 || !grouped) gumbel_words(g.seed, vc, pos >> 2, g.draw, s_slot[r0 + e], words);
+          const int k = pos & 3;
+          const float nz = gumbel_of_word(k == 0 ? words[0] : k == 1 ? words[1] : k == 2 ? words[2] : words[3]);
+#pragma unroll
+          for (int f = 0; f < 4; ++f)
+            if (f == e) z[f] = z[f] * g.inv_temp + nz;
+        }
+      }
+      int bi[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        bi[e] = vc < g.V ? vc : 0x7FFFFFFF;
+        if (vc >= g.V) z[e] = -INFINITY;
+      }
+      row_best_to_lds(z, bi, col, s_bv[n] + r0, s_bi[n] + r0);
+    }
+  }
+  if constexpr (EPI == BEPI_ARGMAX) {
+    __syncthreads();
+    if (tid < MT * 16 && tid < g.Mt * 16) {
+      float v = s_bv[0][tid];
+      int ix = s_bi[0][tid];
+#pragma unroll
+      for (int n = 1; n < TN; ++n) {
+        if (nt0 + n >= g.Nt) break;
+        const float ov = s_bv[n][tid];
+        const int oi = s_bi[n][tid];
+        if (ov > v || (ov == v && oi < ix)) {
+          v = ov;
+          ix = oi;
+        }
+      }
+      g.pmax[(long)ng * g.pld + tid] = v;
+      g.pidx[(long)ng * g.pld + tid] = ix;
+    }
+  }
+}
+
 // best over the LM head's n-groups, per row (one wave per row)
 __global__ __launch_bounds__(64) void k_bargmax(const float* pmax, const int* pidx, int ngroups, int pld, int M,
                                                 int* tokens) {
@@ -520,24 +714,47 @@ __global__ __launch_bounds__(64) void k_bargmax(const float* pmax, const int* pi
 }
 
 
-// RMSNorm of row blockIdx.x of X [M, H] (fp32) with gain g into fp16 A fragments.  One
-// work-group of 256 threads per row, 8 consecutive columns per thread and step.
-__global__ __launch_bounds__(256) void k_bnorm(const float* X, int H, const float* gain, float eps, u32x4* A,
-                                               int a_kt) {
+// RMSNorm of row blockIdx.x of X [M, H] (fp32) with gain g into fp16 A fragments; with kg > 0 the
+// row first receives the kg K parts that the projection before it left ([kg][ld_rows][H], added
+// in K order).  One work-group of 256 threads per row, 8 consecutive columns per thread and step.
+__global__ __launch_bounds__(256) void k_bnorm(float* X, int H, const float* part, int kg, long ld_rows,
+                                               const float* gain, float eps, u32x4* A, int a_kt) {
+  constexpr int kMaxChunks = 4;  // H <= 8192
   __shared__ float red[4];
   const int row = blockIdx.x;
-  const float* x = X + (long)row * H;
+  float* x = X + (long)row * H;
+  f32x4 u[kMaxChunks][2];
   float sq = 0.f;
-  for (int k0 = threadIdx.x * 8; k0 < H; k0 += 2048) {
-    const f32x4 a = *reinterpret_cast<const f32x4*>(x + k0), b = *reinterpret_cast<const f32x4*>(x + k0 + 4);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) sq += a[e] * a[e] + b[e] * b[e];
+  for (int c = 0; c < kMaxChunks; ++c) {
+    const int k0 = threadIdx.x * 8 + c * 2048;
+    if (k0 >= H) break;
+    u[c][0] = *reinterpret_cast<const f32x4*>(x + k0);
+    u[c][1] = *reinterpret_cast<const f32x4*>(x + k0 + 4);
+    if (kg > 0) {
+      f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll 4
+      for (int z = 0; z < kg; ++z) {
+        const f32x4* p = reinterpret_cast<const f32x4*>(part + ((long)z * ld_rows + row) * H + k0);
+        s[0] += p[0];
+        s[1] += p[1];
+      }
+      u[c][0] += s[0];
+      u[c][1] += s[1];
+      *reinterpret_cast<f32x4*>(x + k0) = u[c][0];
+      *reinterpret_cast<f32x4*>(x + k0 + 4) = u[c][1];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sq += u[c][0][e] * u[c][0][e] + u[c][1][e] * u[c][1][e];
   }
   const float rstd = rsqrtf(block_sum256(sq, red) / H + eps);
-  for (int k0 = threadIdx.x * 8; k0 < H; k0 += 2048) {
+#pragma unroll
+  for (int c = 0; c < kMaxChunks; ++c) {
+    const int k0 = threadIdx.x * 8 + c * 2048;
+    if (k0 >= H) break;
     float v[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = x[k0 + e] * rstd * gain[k0 + e];
+    for (int e = 0; e < 8; ++e) v[e] = u[c][e >> 2][e & 3] * rstd * gain[k0 + e];
     A[frag_off(row, k0, a_kt) >> 3] = pack_h8(v);
   }
 }
@@ -1017,12 +1234,40 @@ void launch_bgemm(hipStream_t s, int epi, const BGemmArgs& g, const BRows& rows)
   }
 }
 
+// (MT, TN, NS) of the shapes that the plan chooses: NS k-tiles in flight as the registers allow
+template <int EPI>
+static void launch_bstream_e(hipStream_t s, const BGemmArgs& g, const BRows& rows) {
+  const dim3 grid((g.Nt + g.nw - 1) / g.nw * g.kg * g.layers);
+  auto go = [&](auto k) { hipLaunchKernelGGL(k, grid, dim3(256), 0, s, g, rows); };
+  if (g.Mt > 4) return go(k_bstream<EPI, 8, 2, 3>);
+  if constexpr (EPI == BEPI_RESID) {
+    if (g.Mt <= 1) go(k_bstream<EPI, 1, 4, 6>);
+    else if (g.Mt <= 2) go(k_bstream<EPI, 2, 4, 6>);
+    else go(k_bstream<EPI, 4, 4, 4>);
+  } else {
+    if (g.Mt <= 1) go(k_bstream<EPI, 1, 2, 8>);
+    else if (g.Mt <= 2) go(k_bstream<EPI, 2, 2, 8>);
+    else if (g.nw == 4) go(k_bstream<EPI, 4, 4, 4>);
+    else go(k_bstream<EPI, 4, 2, 6>);
+  }
+}
+
+void launch_bstream(hipStream_t s, int epi, const BGemmArgs& g, const BRows& rows) {
+  switch (epi) {
+    case BEPI_QKV: launch_bstream_e<BEPI_QKV>(s, g, rows); break;
+    case BEPI_RESID: launch_bstream_e<BEPI_RESID>(s, g, rows); break;
+    case BEPI_SWIGLU: launch_bstream_e<BEPI_SWIGLU>(s, g, rows); break;
+    default: launch_bstream_e<BEPI_ARGMAX>(s, g, rows); break;
+  }
+}
+
 void launch_bargmax(hipStream_t s, const float* pmax, const int* pidx, int ngroups, int pld, int M, int* tokens) {
   hipLaunchKernelGGL(k_bargmax, dim3(M), dim3(64), 0, s, pmax, pidx, ngroups, pld, M, tokens);
 }
 
-void launch_bnorm(hipStream_t s, const float* X, int M, int H, const float* gain, float eps, u32x4* A, int a_kt) {
-  hipLaunchKernelGGL(k_bnorm, dim3(M), dim3(256), 0, s, X, H, gain, eps, A, a_kt);
+void launch_bnorm(hipStream_t s, float* X, int M, int H, const float* part, int kg, long ld_rows, const float* gain,
+                  float eps, u32x4* A, int a_kt) {
+  hipLaunchKernelGGL(k_bnorm, dim3(M), dim3(256), 0, s, X, H, part, kg, ld_rows, gain, eps, A, a_kt);
 }
 
 void launch_bembed_norm(hipStream_t s, const uint16_t* embed, const int32_t* ids, int M, int H, int V,

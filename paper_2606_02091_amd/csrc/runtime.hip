@@ -679,15 +679,19 @@ int build(dflare_handle* h, const dflare_weights* w) {
       need("KVT", Nt_kvt, mt, Kt_H, D);
       if (c.variant & DFLARE_VARIANT_DFLASH) need("FC", H / 16, mt, S * H / 32, 1);
     }
+    // K parts of the few-row residual projections, plain rows
+    part = std::max(part, (long)kBSplitMax * std::min(h->b_mt, kBStreamMt) * 16 * H);
     h->bpart_floats = part;
     TRY(dev_alloc(h, &h->bpart, (size_t)std::max(part, 64L) * 4));
     TRY(dev_zalloc(h, &h->bcnt, (size_t)kBCounters * 128));
     const long items = (long)c.max_batch * ceil_div((long)c.max_context + B, kBKeys) * c.n_kv_heads;
     TRY(dev_alloc(h, &h->bOP, (size_t)items * h->Rpad * hd * 4));
     TRY(dev_alloc(h, &h->bML, (size_t)items * h->Rpad * sizeof(float2)));
-    const long ng_lm = ceil_div(Nt_lm, kBN);
-    TRY(dev_alloc(h, &h->bpmax, (size_t)ng_lm * rows * 4));
-    TRY(dev_alloc(h, &h->bpidx, (size_t)ng_lm * rows * 4));
+    // best (score, id) per group of output tiles and row (few-row calls: groups of 2 or 4 tiles)
+    const long best = std::max((long)ceil_div(Nt_lm, kBN) * rows,
+                               (long)ceil_div(Nt_lm, 2) * std::min(h->b_mt, kBStreamMt) * 16);
+    TRY(dev_alloc(h, &h->bpmax, (size_t)best * 4));
+    TRY(dev_alloc(h, &h->bpidx, (size_t)best * 4));
   }
   if (c.max_batch > 1 || (c.variant & DFLARE_VARIANT_DFLASH)) TRY(ensure_f16_weights(h));
   HIP_OR_FAIL(h, hipHostMalloc((void**)&h->err_host, 64, hipHostMallocMapped | hipHostMallocCoherent));
@@ -934,16 +938,60 @@ int ensure_f16_weights(dflare_handle* h) {
   return check_launch(h, "weight conversion");
 }
 
-// one batched GEMM with its fused epilogue; the K split is chosen per shape
-void bgemm(dflare_handle* h, int kind, const char* name, int epi, BGemmArgs g, const BRows& rows) {
-  g.nw = bgemm_nw(h->cus, name, g.Nt, g.Mt, g.Kt, g.layers, epi != BEPI_ARGMAX && epi != BEPI_BIAS16);
-  g.kg = bgemm_split(h->cus, name, g.Nt, g.Mt, g.Kt, g.layers, epi != BEPI_ARGMAX, g.nw);
+// Shape of a GEMM of few rows on k_bstream: output tiles per work-group (tn) and K parts (kg, only
+// where the epilogue is linear in the sum); tn = 0: the tiled kernel runs it better.  Two forces:
+// a work-group reads all rows of A, so wide ones (tn = 4) read less, and the weights stream at
+// full rate only with enough work-groups.
+//   - Residual projections can split K: tn = 4 with one work-group per CU (H = 4,096, 4 sequences:
+//     output 17 us, down 31; tn = 2 without the split 25 and 60), at more than four row tiles tn = 2
+//     (two accumulator sets of eight row tiles fill the registers) and two per CU.
+//   - The others: tn = 2, and 4 for three or four row tiles once that leaves a work-group per CU
+//     (gate/up of 1,536 tiles at 64 rows 54 against 58 us; Q/K/V of 384 tiles 28 against 23).
+//   - More than four row tiles: only while two work-groups per CU hold the whole GEMM (Q/K/V of
+//     384 tiles at 128 rows 30 us, tiled 51; gate/up of 1,536 tiles 73, tiled 69).
+struct StreamShape {
+  int tn, kg;
+};
+StreamShape bstream_shape(int cus, int epi, int Nt, int Mt, int Kt, int layers) {
+  StreamShape s{0, 1};
+  if (Mt > kBStreamMt || epi == BEPI_BIAS16) return s;
+  if (epi == BEPI_RESID) {
+    s.tn = Mt <= 4 ? 4 : 2;
+    const long slots = Mt <= 4 ? cus : 2L * cus;
+    for (int kg : {2, 3, 4, 6, 8})
+      if ((long)ceil_div(Nt, s.tn) * kg <= slots && Kt >= 16 * kg) s.kg = kg;
+  } else if (Mt <= 4) {
+    s.tn = Mt > 2 && (long)ceil_div(Nt, 4) * layers >= cus ? 4 : 2;
+  } else if ((long)ceil_div(Nt, 2) * layers <= 2L * cus) {
+    s.tn = 2;
+  }
+  return s;
+}
+
+// one batched GEMM with its fused epilogue; tile and K split are chosen per shape.  Returns the
+// number of K parts that a residual projection has left for the norm that follows (0: its sums are
+// in X already).
+int bgemm(dflare_handle* h, int kind, const char* name, int epi, BGemmArgs& g, const BRows& rows) {
   g.zero = h->zero_tile;
   g.part = h->bpart;
   g.cnt = h->bcnt;
+  const StreamShape ss = bstream_shape(h->cus, epi, g.Nt, g.Mt, g.Kt, g.layers);
   prof_mark(h, kind, true);
-  launch_bgemm(h->stream, epi, g, rows);
+  if (ss.tn) {
+    g.nw = ss.tn;
+    g.kg = ss.kg;
+    g.pld = g.Mt * 16;
+    g.n_groups = ceil_div(g.Nt, ss.tn);
+    launch_bstream(h->stream, epi, g, rows);
+  } else {
+    g.nw = bgemm_nw(h->cus, name, g.Nt, g.Mt, g.Kt, g.layers, epi != BEPI_ARGMAX && epi != BEPI_BIAS16);
+    g.kg = bgemm_split(h->cus, name, g.Nt, g.Mt, g.Kt, g.layers, epi != BEPI_ARGMAX, g.nw);
+    g.pld = h->b_mt * 16;
+    g.n_groups = ceil_div(g.Nt, kBWaves * g.nw);
+    launch_bgemm(h->stream, epi, g, rows);
+  }
   prof_mark(h, kind, false);
+  return ss.tn && epi == BEPI_RESID ? ss.kg : 0;
 }
 
 // epilogue fields shared by every batched GEMM of a handle
@@ -969,7 +1017,6 @@ BGemmArgs bgemm_base(const dflare_handle* h) {
   g.V = c.vocab;
   g.pmax = h->bpmax;
   g.pidx = h->bpidx;
-  g.pld = h->b_mt * 16;
   return g;
 }
 
@@ -1089,9 +1136,9 @@ int run_draft_batched(dflare_handle* h, int n_seq, const int32_t* seq, const int
     g.W = h->h_o + l * h->s_o;
     g.Nt = Nt_H;
     g.Kt = Kt_q;
-    bgemm(h, DFLARE_K_B_O, "O", BEPI_RESID, g, rows);
+    int kg = bgemm(h, DFLARE_K_B_O, "O", BEPI_RESID, g, rows);
     prof_mark(h, DFLARE_K_B_EPI, true);
-    launch_bnorm(s, h->bX, M, H, h->g_mlp + (long)l * H, c.rms_eps, h->bA, Kt_H);
+    launch_bnorm(s, h->bX, M, H, h->bpart, kg, Mt * 16L, h->g_mlp + (long)l * H, c.rms_eps, h->bA, Kt_H);
     prof_mark(h, DFLARE_K_B_EPI, false);
     g.A = h->bA;
     g.W = h->h_gu + l * h->s_gu;
@@ -1102,9 +1149,9 @@ int run_draft_batched(dflare_handle* h, int n_seq, const int32_t* seq, const int
     g.W = h->h_down + l * h->s_down;
     g.Nt = Nt_H;
     g.Kt = Kt_F;
-    bgemm(h, DFLARE_K_B_DOWN, "DOWN", BEPI_RESID, g, rows);
+    kg = bgemm(h, DFLARE_K_B_DOWN, "DOWN", BEPI_RESID, g, rows);
     prof_mark(h, DFLARE_K_B_EPI, true);
-    launch_bnorm(s, h->bX, M, H, (l + 1 < D) ? h->g_attn + (long)(l + 1) * H : h->g_final, c.rms_eps, h->bA, Kt_H);
+    launch_bnorm(s, h->bX, M, H, h->bpart, kg, Mt * 16L, (l + 1 < D) ? h->g_attn + (long)(l + 1) * H : h->g_final, c.rms_eps, h->bA, Kt_H);
     prof_mark(h, DFLARE_K_B_EPI, false);
   }
   g.A = h->bA;
@@ -1118,7 +1165,7 @@ int run_draft_batched(dflare_handle* h, int n_seq, const int32_t* seq, const int
   if (h->temperature > 0.f) ++h->draw;
   prof_mark(h, DFLARE_K_B_LM_HEAD, true);
   bgemm(h, -1, "LM", BEPI_ARGMAX, g, rows);  // timed with the final argmax below
-  launch_bargmax(s, h->bpmax, h->bpidx, ceil_div(Nt_lm, kBN), g.pld, M, out);
+  launch_bargmax(s, h->bpmax, h->bpidx, g.n_groups, g.pld, M, out);
   prof_mark(h, DFLARE_K_B_LM_HEAD, false);
   if (h->debug) h->dbg_blogits_rows = M;
   return check_launch(h, "draft_block_batched");

@@ -22,6 +22,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import dflare_oracle as orc
 from paper_2606_02091_amd import dflare as dfl
 from paper_2606_02091_amd import synth
 import parity as P
@@ -147,6 +148,31 @@ def test_batched_matches_oracles(name):
     for j, s in enumerate(sub):
         i = slots.index(s)
         assert P.relinf(l2[j], logits[i]) <= AGREE_TOL
+    model.close()
+
+
+# calls of one to eight row tiles (the weight-streaming GEMM picks its shape by them), ragged rows
+# (B = 13); k-tiles per wave from none (H = 96: three k-tiles for four waves) to several, residual
+# projections with and without a K split (q = 1,024, F = 2,080), greedy and sampled
+@pytest.mark.parametrize("hidden,n_q,n_kv,hd,ffn", [(96, 4, 2, 64, 160), (1056, 8, 2, 128, 2080)])
+def test_batched_few_rows(hidden, n_q, n_kv, hd, ffn):
+    cfg = synth.ModelConfig("few", hidden=hidden, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=hd, ffn=ffn, vocab=1001,
+                            n_draft_layers=2, n_target_layers=3, block_size=13, context=40, random_block=True)
+    slots = [5, 0, 3, 9, 1, 7, 2, 8, 4]
+    print(f"[batched] few rows H={hidden}", flush=True)
+    model, orcs, _ = build_batched(cfg, [40, 7, 0, 16, 33, 1, 12, 25, 18], slots, 10)
+    for n in (1, 2, 3, 4, 5, 6, 9):
+        tokens, logits, worst = compare_draft(model, orcs, cfg, slots[:n])
+        print(f"[batched] few rows H={hidden}: {n} sequences, logits rel err {worst:.2e}", flush=True)
+        dfl.dflare_set_sampling(model.h, 0.8, 11)
+        ids = np.stack([slot_ids(cfg, s) for s in slots[:n]])
+        drawn = model.draft_block_batched(slots[:n], ids_tensor(ids)).cpu().numpy()
+        for i, s in enumerate(slots[:n]):
+            want, scores = orc.sample_tokens(logits[i].astype(np.float64), 0.8, 11, 0, slot=s)
+            # the scores of the kernel's own logits, in fp32: the noise's logarithms err by 1e-5 at most
+            for b in range(cfg.block_size):
+                assert scores[b][drawn[i][b]] >= scores[b][want[b]] - 1e-4, (n, s, b)
+        dfl.dflare_set_sampling(model.h, 0.0, 0)
     model.close()
 
 
