@@ -458,11 +458,11 @@ int dflare_read_probe(const void* buf, int64_t bytes, uint32_t* sink, void* stre
  *   out            DEVICE fp32 [n_blocks*B, n_q, hd];  lse  DEVICE fp32 [n_blocks*B, n_q]
  *                  (natural log-sum-exp of each row's scaled scores, for the backward pass)
  *   workspace      DEVICE scratch of at least dflare_anchor_attention_workspace(...) bytes
- *                  (transposed copies and partial sums; contents need not be kept)
+ *                  (operand copies and partial sums; contents need not be kept)
  * Supported: 1 <= B <= 16, hd 64 or 128, (n_q / n_kv) * B <= 128; else UNSUPPORTED.  The
  * products run on bf16 matrix cores (probabilities and gradients rounded to bf16 as operands,
  * fp32 accumulation).  Asynchronous on `stream` (hipStream_t, NULL = default).  Gradients are
- * deterministic: context-key gradients are summed over chunks of 64 blocks in a fixed order.
+ * deterministic: context-key gradients are summed over chunks of at most 64 blocks in a fixed order.
  */
 size_t dflare_anchor_attention_workspace(int32_t n_blocks, int32_t B, int32_t T, int32_t n_q, int32_t n_kv,
                                          int32_t hd);

@@ -14,9 +14,6 @@ INCLUDE = os.path.join(ROOT, "include")
 LIBDIR = os.path.join(PKG, "_lib")
 LIB = os.path.join(LIBDIR, "libdflare.so")
 SOURCES = ["kernels.hip", "batched.hip", "runtime.hip", "training.hip"]
-# per-source flags: the training kernels keep their matrix-core accumulators in ordinary
-# vector registers (the accumulation-register form made the compiler copy them every tile)
-EXTRA_FLAGS = {"training.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 ARCH = os.environ.get("DFLARE_OFFLOAD_ARCH", "gfx950")
 
 
@@ -35,7 +32,7 @@ def build(verbose: bool = False) -> str:
               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
               "-I", INCLUDE, "-I", CSRC, "-Wall", "-Wno-unused-function"]
     objs = [os.path.join(LIBDIR, src.replace(".hip", ".o")) for src in SOURCES]
-    cmds = [[hipcc(), *common, *EXTRA_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
+    cmds = [[hipcc(), *common, "-c", os.path.join(CSRC, src), "-o", obj]
             for src, obj in zip(SOURCES, objs)]
     # the translation units are independent: compile them side by side
     with ThreadPoolExecutor(max_workers=len(cmds)) as ex:

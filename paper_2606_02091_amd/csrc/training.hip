@@ -7,13 +7,17 @@
 //     w_k = exp(-(k - 1) / gamma) on the k-th masked position of each block, the loss is
 //     their weighted mean; forward and the gradient of the logits.
 //
-// Matrix products run on v_mfma_f32_16x16x32_bf16 with every operand read straight from
-// memory in its operand layout: scores are formed transposed (S^T = K Q^T) where the
-// probabilities feed a product over keys (P V, dS K), and untransposed (S = Q K^T) where they
-// feed a product over query rows (P^T dO, dS^T Q).  The operands that need the other
-// orientation (V^T, K^T, Q^T, dO^T) are written once per call into the workspace by
-// transposing kernels; two 16-key (or 16-row) result tiles of a lane hold keys 4q..4q+3 and
-// 16+4q..16+4q+3, so the matching operand is read as two 8-byte pieces.
+// Matrix products run on the bf16 matrix cores.  Scores are formed transposed (S^T = K Q^T) where
+// the probabilities feed a product over keys (P V, dS K), and untransposed (S = Q K^T) where they
+// feed a product over query rows (P^T dO, dS^T Q), so that the score tile a wave has just computed
+// is the other product's B operand without leaving the registers.  That product's A operand is a
+// transposed tile (V^T, K^T, Q^T, dO^T), read from LDS by the transposing read (ds_read_b64_tr_b16), so
+// no transposed copy exists anywhere.
+//
+// Tiles reach LDS through registers, a tile ahead: loaded while the tile before is worked on, stored
+// after the barrier that ends it.  LDS-direct loads would save these registers, but the compiler waits
+// for all of them before any LDS read that follows, so that a tile's products waited for the loads
+// just issued for the next (context dK, dV of 512 blocks, T = 3,072: 580 against 500 us).
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -29,27 +33,28 @@ namespace dflare {
 namespace {
 
 constexpr int kTrT = 256;  // threads per work-group (4 waves)
-constexpr int kChunkBlocks = 64;  // blocks per partial of the context-key gradients
+constexpr int kChunkBlocks = 64;  // most blocks per partial of the context-key gradients
 constexpr int kMaxBlockKeys = 16;  // block size B the training entry points accept
+// (block, KV head) pairs up to which a block's key tiles are split over a work-group's waves: above
+// one pair per CU the waves of further blocks occupy the chip without a merge (4 blocks of 64 rows, 8 KV
+// heads, T = 3,072: 48 us split, 79 us with 16-row waves)
+constexpr long kRowsSplitMax = 256;
 
 struct AttnShapeT {
   int n_blocks, B, T, n_q, n_kv, hd;
-  int G, R, Rp, Tp, Mp;  // heads per group, rows per (block, group), padded rows / context keys / block keys
+  int G, R, Rp;  // heads per group, rows per (block, group), the same padded to 32
 };
 
 struct AttnT {
   AttnShapeT s;
   const uint16_t *q, *kc, *vc, *kb, *vb;  // bf16 inputs
   const int32_t* anchors;
-  // workspace (bf16 transposed copies, fp32 partials)
-  uint16_t *kct, *vct, *kbt, *vbt;  // [n_kv][hd][Tp] / [n_kv][hd][n_blocks * 32]
-  uint16_t *qt, *dot, *dob;         // [n_kv][n_blocks][hd][Rp] x2, [M][n_q][hd]
-  uint16_t *qr, *dor;               // [n_kv][n_blocks][Rp][hd] x2 (rows of a (block, group))
-  float2* st;                       // [n_kv][n_blocks][Rp] (lse * log2 e, rowsum(dO O)); (+inf, 0) past R
-  float* dsum;                      // [M][n_q] rowsum(dO * O)
+  // workspace
+  uint16_t *qf, *df;                // [n_kv][n_blocks][Rp / 32][32 x hd] Q and dO (bf16) rows in fragment tiles
+  float* st;                        // [n_kv][n_blocks][2][Rp] -lse / scale, -rowsum(dO O); (-inf, 0) past R
   float* part;                      // [nch][T][n_kv][hd] x2 (dK, dV)
   int* order;                       // [n_blocks] blocks by decreasing anchor (work order)
-  int nch;
+  int nch;                          // chunks of the context-key gradients: chunk z takes order[z], order[z + nch], ...
   // outputs
   float *out, *lse;
   const float* dout;
@@ -58,12 +63,6 @@ struct AttnT {
 };
 
 __device__ __forceinline__ u32x4 ld16(const uint16_t* p) { return *reinterpret_cast<const u32x4*>(p); }
-// keys (or rows) 4q..4q+3 and 16+4q..16+4q+3 of a 32-wide range starting at p
-__device__ __forceinline__ u32x4 ld_pair(const uint16_t* p) {
-  const u32x2 a = *reinterpret_cast<const u32x2*>(p);
-  const u32x2 b = *reinterpret_cast<const u32x2*>(p + 16);
-  return u32x4{a[0], a[1], b[0], b[1]};
-}
 // two fp32 values -> two bf16 (round to nearest even) in one word, by the packed conversion
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -78,689 +77,630 @@ __device__ __forceinline__ u32x4 pack_bf8(f32x4 x, f32x4 y) {
 // resolution) are not kept as denormals; 2^-inf = 0
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }
-// LDS swizzles.  Row tiles (PK 16-byte pieces per row): piece c of row k sits in slot
-// c ^ rsw(k), so that one piece of 16 consecutive rows covers all 64 banks.  Transposed tiles
-// (4 pieces of 8 keys per dim row d): piece c in slot c ^ tsw(d), the same for 16 dim rows.
-template <int PK>
-__device__ __forceinline__ int rsw(int k) {
-  return PK == 16 ? (k & 15) : ((k >> 1) & 7);
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f32x16 mfma32(u32x4 a, u32x4 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                 0, 0);
 }
-__device__ __forceinline__ int tsw(int d) { return (d >> 2) & 3; }
-
-// ---- layout helpers ------------------------------------------------------------------
-// src [rows][n_kv][hd] (bf16) -> dst [n_kv][hd][ld], zeros for rows >= nrows; block
-// (32-row tile, 32-column tile of n_kv*hd) through a padded LDS tile.
-__global__ __launch_bounds__(256) void k_tr_kv_t(const uint16_t* src, int nrows, int cols, int ld, uint16_t* dst) {
-  __shared__ uint16_t tile[32][34];
-  const int r0 = blockIdx.x * 32, c0 = blockIdx.y * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-  for (int y = ty; y < 32; y += 8) {
-    const int r = r0 + y, c = c0 + tx;
-    tile[y][tx] = (r < nrows && c < cols) ? src[(long)r * cols + c] : (uint16_t)0;
-  }
-  __syncthreads();
-  for (int y = ty; y < 32; y += 8) {
-    const int c = c0 + y, r = r0 + tx;
-    if (c < cols && r < ld) dst[(long)c * ld + r] = tile[tx][y];
-  }
-}
-
-// block keys src [n_blocks*B][n_kv][hd] -> dst [n_kv][hd][n_blocks*32]: block i's keys at
-// i*32 + j (j < B), zeros for j >= B, so that every 16-byte piece of a block is aligned.
-// Work-group = (block i, 256 columns): rows read along the columns into an LDS tile, then each
-// column's 32 keys written as four 16-byte pieces.
-__global__ __launch_bounds__(256) void k_tr_blk_t(const uint16_t* src, int n_blocks, int B, int cols, uint16_t* dst) {
-  __shared__ uint16_t tl[256][kMaxBlockKeys + 2];
-  const int i = blockIdx.x, c0 = blockIdx.y * 256, t = threadIdx.x;
-  const long ld = (long)n_blocks * 32;
-  for (int j = 0; j < B; ++j) tl[t][j] = c0 + t < cols ? src[((long)i * B + j) * cols + c0 + t] : (uint16_t)0;
-  __syncthreads();
-  for (int e = t; e < 256 * 4; e += 256) {
-    const int c = e / 4, pc = e % 4;  // column c0 + c, keys 8 pc .. 8 pc + 7
-    if (c0 + c >= cols) continue;
-    uint32_t w[4];
+__device__ __forceinline__ f32x16 splat16(float x) {
+  f32x16 v;
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      const int j = 8 * pc + 2 * h;
-      const uint32_t lo = j < B ? tl[c][j] : 0u, hi = j + 1 < B ? tl[c][j + 1] : 0u;
-      w[h] = lo | (hi << 16);
-    }
-    *reinterpret_cast<u32x4*>(dst + (long)(c0 + c) * ld + (long)i * 32 + 8 * pc) = u32x4{w[0], w[1], w[2], w[3]};
-  }
+  for (int e = 0; e < 16; ++e) v[e] = x;
+  return v;
+}
+// registers 8 ks .. 8 ks + 7 of a 32 x 32 result tile as one bf16 operand (16 values of k)
+__device__ __forceinline__ u32x4 pack_half(const f32x16& x, int ks) {
+  return u32x4{cvt_bf2(x[8 * ks], x[8 * ks + 1]), cvt_bf2(x[8 * ks + 2], x[8 * ks + 3]),
+               cvt_bf2(x[8 * ks + 4], x[8 * ks + 5]), cvt_bf2(x[8 * ks + 6], x[8 * ks + 7])};
 }
 
-// ---- backward operands of (block i, KV head g), one work-group each.  Row r < R of the pair
-// is block position r % B of query head g G + r / B; a row is read once (Q, dO, O: HD / 4
-// threads, four dims each) and gives dO in bf16 (dob, the input layout), D = rowsum(dO O)
-// (dsum), the grouped row copies qr and dor, the pair (lse log2 e, D) (st), and, through an
-// LDS tile, the transposed copies qt and dot.  Rows R .. Rp-1 are zeros (st: (+inf, 0)).  The
-// LDS tiles [2][HD][Rp] keep each 32-row group with its rows permuted per dim row (r ^ (2
-// (d / 4) mod 32)), so that the row-wise writes spread over the banks. ----
+// barrier that waits for this wave's LDS operations only: its loads into registers stay in flight
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// ---- fragment tiles: 32 rows of HD bf16, in memory and in LDS alike.  The 16-byte piece c = 2 k + h of
+// a row is an operand's piece for k-step k and lane half h: fragment k is 1 KB, piece (row, h) in slot
+// 32 h + (row ^ (4 h + 8 (k mod 2))).  An untransposed operand is one fragment (contiguous for a
+// wave); a transposed read covers 4 rows x 32 columns per half wave, and the xor puts these in
+// 256 different bytes modulo the bank cycle. ----
 template <int HD>
-__global__ __launch_bounds__(256) void k_bwd_prep(const uint16_t* q, const float* dout, const float* out,
-                                                   const float* lse, AttnShapeT s, uint16_t* dob, float* dsum,
-                                                   uint16_t* qr, uint16_t* dor, float2* st, uint16_t* qt,
-                                                   uint16_t* dot) {
-  extern __shared__ uint16_t tl[];
-  constexpr int TPR = HD / 4, RPS = 256 / TPR;
-  const int i = blockIdx.x, g = blockIdx.y;
-  const int c4 = threadIdx.x % TPR, rs = threadIdx.x / TPR;
-  const int d0 = 4 * c4;
-  const int swz = (2 * c4) & 31;
+constexpr int kTileBytes = 32 * HD * 2;
+__device__ __forceinline__ int frag_slot(int row, int h, int kodd) { return 32 * h + (row ^ (4 * h + 8 * kodd)); }
+// byte offset of piece c of a row
+__device__ __forceinline__ int piece_at(int row, int c) {
+  return (c >> 1) * 1024 + frag_slot(row, c & 1, (c >> 1) & 1) * 16;
+}
+// Transposed read of 4 rows r0 .. r0 + 3 x 16 columns 16 k ..: lane i of a 16-lane group gets column
+// 16 k + i of the 4 rows; its address (a byte offset here) is that of row r0 + i / 4, columns
+// 16 k + 4 (i mod 4).  The group's r0 and k may differ from the other groups'.
+__device__ __forceinline__ int tr_at(int r0, int k, int lane) {
+  const int i = lane & 15;
+  return piece_at(r0 + (i >> 2), 2 * k + ((i >> 1) & 1)) + (i & 1) * 8;
+}
+__device__ __forceinline__ u32x2 ld_tr(const char* p) {
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDSP s16x4*)(LDSP char*)const_cast<char*>(p)));
+}
+// A operand (32 x 16) of a transposed tile: output rows = columns 32 dt + (0..31), k = rows
+// 16 ks + {4 h .. 4 h + 3, 8 + 4 h .. 8 + 4 h + 3} in lane half h -- the rows whose values a 32 x 32
+// result tile holds in registers 8 ks .. 8 ks + 7 of that half.
+__device__ __forceinline__ u32x4 ld_tr_op(const char* tile, const int (&off)[2], int ks, int dt) {
+  const u32x2 lo = ld_tr(tile + dt * 2048 + ks * 256 + off[0]);
+  const u32x2 hi = ld_tr(tile + dt * 2048 + ks * 256 + off[1]);
+  return u32x4{lo[0], lo[1], hi[0], hi[1]};
+}
+__device__ __forceinline__ void tr_offsets(int lane, int (&off)[2]) {
+#pragma unroll
+  for (int x = 0; x < 2; ++x) off[x] = tr_at(8 * x + 4 * (lane >> 5), (lane >> 4) & 1, lane);
+}
+// this lane's byte offset in fragment k of an untransposed operand: o[k mod 2] + 1024 k
+__device__ __forceinline__ void frag_offsets(int lane, int (&o)[2]) {
+#pragma unroll
+  for (int x = 0; x < 2; ++x) o[x] = frag_slot(lane & 31, lane >> 5, x) * 16;
+}
+__device__ __forceinline__ u32x4 ld16b(const char* p) { return *reinterpret_cast<const u32x4*>(p); }
+
+// Work-group n of a launch over (unit, KV head) pairs.  Work-groups go to the 8 XCDs in turn, each with an
+// L2 of its own; an XCD takes every 8th unit and, one after another, all KV heads of it.  So the
+// work-groups that run together on an XCD read all heads: rows of one head alone lie a whole
+// row of heads apart and would meet in a few of the L2's channels.
+__device__ __forceinline__ void unit_head(int n, int n_kv, int& unit, int& g) {
+  const int m = n / 8;
+  g = m % n_kv;
+  unit = m / n_kv * 8 + n % 8;
+}
+
+// ---- backward operands and block-key gradients of (block i, KV head g), one work-group each.  Row
+// r < R of the pair is block position r % B of query head g G + r / B; a row is read once (Q, dO, O: 16
+// bytes of bf16 per thread and piece) and gives -lse / scale and -rowsum(dO O) (st; (-inf, 0) past R) and
+// the fragment tiles of Q and dO, in LDS and copied out (qf, df).  From these every wave
+// forms S and dP of all rows against the block's B keys and adds up dK and dV of its HD / 4 dims. ----
+template <int HD>
+__global__ __launch_bounds__(kTrT) void k_bwd_prep(AttnT a, const float* out) {
+  extern __shared__ char sm[];
+  constexpr int PK = HD / 8, RPS = kTrT / PK;
+  const AttnShapeT& s = a.s;
+  int i, g;
+  unit_head(blockIdx.x, s.n_kv, i, g);
+  if (i >= s.n_blocks) return;
+  char* tq = sm;
+  char* td = sm + s.Rp * HD * 2;
+  float* snl = reinterpret_cast<float*>(sm + 2 * s.Rp * HD * 2);
+  float* snd = snl + s.Rp;
   const long tile = (long)g * s.n_blocks + i;
-  uint16_t* tlq = tl;
-  uint16_t* tld = tl + HD * s.Rp;
-  for (int r = rs; r < s.Rp; r += RPS) {
-    const bool rv = r < s.R;
-    const long rh = rv ? (long)(i * s.B + r % s.B) * s.n_q + g * s.G + r / s.B : 0;
-    f32x4 x = zero4(), o = zero4();
-    u32x2 qv = {0u, 0u};
-    if (rv) {
-      x = *reinterpret_cast<const f32x4*>(dout + rh * HD + d0);
-      o = *reinterpret_cast<const f32x4*>(out + rh * HD + d0);
-      qv = *reinterpret_cast<const u32x2*>(q + rh * HD + d0);
-    }
-    float acc = (x[0] * o[0] + x[1] * o[1]) + (x[2] * o[2] + x[3] * o[3]);
+  const float rscale = 1.f / a.scale, sl2 = a.scale * 1.4426950408889634f;
+  {
+    const int c = threadIdx.x % PK, rs = threadIdx.x / PK;
+    for (int r = rs; r < s.Rp; r += RPS) {
+      const bool rv = r < s.R;
+      const long rh = rv ? (long)(i * s.B + r % s.B) * s.n_q + g * s.G + r / s.B : 0;
+      f32x4 x0 = zero4(), x1 = zero4(), o0 = zero4(), o1 = zero4();
+      u32x4 qv = {0u, 0u, 0u, 0u};
+      if (rv) {
+        const f32x4* px = reinterpret_cast<const f32x4*>(a.dout + rh * HD + 8 * c);
+        const f32x4* po = reinterpret_cast<const f32x4*>(out + rh * HD + 8 * c);
+        x0 = px[0];
+        x1 = px[1];
+        o0 = po[0];
+        o1 = po[1];
+        qv = ld16(a.q + rh * HD + 8 * c);
+      }
+      const f32x4 pr = x0 * o0 + x1 * o1;
+      float acc = (pr[0] + pr[1]) + (pr[2] + pr[3]);
 #pragma unroll
-    for (int off = TPR / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-    const u32x2 dv = {f2bf(x[0]) | (f2bf(x[1]) << 16), f2bf(x[2]) | (f2bf(x[3]) << 16)};
-    if (rv) *reinterpret_cast<u32x2*>(dob + rh * HD + d0) = dv;
-    *reinterpret_cast<u32x2*>(qr + (tile * s.Rp + r) * HD + d0) = qv;
-    *reinterpret_cast<u32x2*>(dor + (tile * s.Rp + r) * HD + d0) = dv;
-    const int rr = (r & ~31) | ((r & 31) ^ swz);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      tlq[(d0 + e) * s.Rp + rr] = (uint16_t)(qv[e >> 1] >> (16 * (e & 1)));
-      tld[(d0 + e) * s.Rp + rr] = (uint16_t)(dv[e >> 1] >> (16 * (e & 1)));
+      for (int off = PK / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+      const u32x4 dv = {f2bf(x0[0]) | (f2bf(x0[1]) << 16), f2bf(x0[2]) | (f2bf(x0[3]) << 16),
+                        f2bf(x1[0]) | (f2bf(x1[1]) << 16), f2bf(x1[2]) | (f2bf(x1[3]) << 16)};
+      const int at = (r >> 5) * kTileBytes<HD> + piece_at(r & 31, c);
+      *reinterpret_cast<u32x4*>(tq + at) = qv;
+      *reinterpret_cast<u32x4*>(td + at) = dv;
+      if (c == 0) {
+        const float nl = rv ? -a.lse[rh] * rscale : -INFINITY;
+        snl[r] = a.st[tile * 2 * s.Rp + r] = nl;
+        snd[r] = a.st[(tile * 2 + 1) * s.Rp + r] = rv ? -acc : 0.f;
+      }
     }
-    if (c4 == 0) {
-      if (rv) dsum[rh] = acc;
-      st[tile * s.Rp + r] = rv ? make_float2(lse[rh] * 1.4426950408889634f, acc) : make_float2(INFINITY, 0.f);
+  }
+  // B operand columns (keys) of this lane: key `col`; keys past B repeat key 0 and are not stored
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int col = lane & 15, q4 = lane >> 4;
+  u32x4 kf[HD / 32], vf[HD / 32];
+  {
+    const long row = ((long)(i * s.B + (col < s.B ? col : 0)) * s.n_kv + g) * HD;
+#pragma unroll
+    for (int ks = 0; ks < HD / 32; ++ks) {
+      kf[ks] = ld16(a.kb + row + ks * 32 + 8 * q4);
+      vf[ks] = ld16(a.vb + row + ks * 32 + 8 * q4);
     }
   }
   __syncthreads();
-  // transposed copies [g][i][d][Rp]: rows r, r + 1 of dim row d per 4-byte store
-  const int half = s.Rp / 2;
-  for (int e = threadIdx.x; e < HD * half; e += 256) {
-    const int d = e / half, r = 2 * (e % half);
-    const int rr = (r & ~31) | ((r & 31) ^ ((2 * (d >> 2)) & 31));
-    const long dst = (tile * HD + d) * s.Rp + r;
-    *reinterpret_cast<uint32_t*>(qt + dst) = *reinterpret_cast<const uint32_t*>(tlq + d * s.Rp + rr);
-    *reinterpret_cast<uint32_t*>(dot + dst) = *reinterpret_cast<const uint32_t*>(tld + d * s.Rp + rr);
+  {
+    const long bytes = (long)s.Rp * HD * 2;
+    char* qd = reinterpret_cast<char*>(a.qf) + tile * bytes;
+    char* dd = reinterpret_cast<char*>(a.df) + tile * bytes;
+    for (int e = threadIdx.x * 16; e < bytes; e += kTrT * 16) {
+      *reinterpret_cast<u32x4*>(qd + e) = ld16b(tq + e);
+      *reinterpret_cast<u32x4*>(dd + e) = ld16b(td + e);
+    }
+  }
+  constexpr int DT = HD / 64;  // 16-dim tiles per wave
+  f32x4 dk[DT], dv[DT];
+#pragma unroll
+  for (int t = 0; t < DT; ++t) dk[t] = dv[t] = zero4();
+  for (int r0 = 0; r0 < s.Rp; r0 += 32) {
+    f32x4 P[2], dS[2];
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+      const f32x4 nl = *reinterpret_cast<const f32x4*>(snl + r0 + 16 * y + 4 * q4);
+      f32x4 sc = zero4(), dp = *reinterpret_cast<const f32x4*>(snd + r0 + 16 * y + 4 * q4);
+#pragma unroll
+      for (int ks = 0; ks < HD / 32; ++ks) {
+        const int at = r0 * HD * 2 + piece_at(16 * y + col, ks * 4 + q4);
+        sc = mfma(*reinterpret_cast<const u32x4*>(tq + at), kf[ks], sc);
+        dp = mfma(*reinterpret_cast<const u32x4*>(td + at), vf[ks], dp);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        P[y][e] = ex2((sc[e] + nl[e]) * sl2);
+        dS[y][e] = P[y][e] * dp[e];
+      }
+    }
+    const u32x4 pb = pack_bf8(P[0], P[1]), sb = pack_bf8(dS[0], dS[1]);
+#pragma unroll
+    for (int t = 0; t < DT; ++t) {
+      const int lo = r0 * HD * 2 + tr_at(4 * q4, w * DT + t, lane), hi = r0 * HD * 2 + tr_at(16 + 4 * q4, w * DT + t, lane);
+      const u32x2 d0 = ld_tr(td + lo), d1 = ld_tr(td + hi), q0 = ld_tr(tq + lo), q1 = ld_tr(tq + hi);
+      dv[t] = mfma(u32x4{d0[0], d0[1], d1[0], d1[1]}, pb, dv[t]);
+      dk[t] = mfma(u32x4{q0[0], q0[1], q1[0], q1[1]}, sb, dk[t]);
+    }
+  }
+  if (col < s.B) {
+#pragma unroll
+    for (int t = 0; t < DT; ++t) {
+      const long at = ((long)(i * s.B + col) * s.n_kv + g) * HD + (w * DT + t) * 16 + 4 * q4;
+      *reinterpret_cast<f32x4*>(a.dkb + at) = dk[t] * a.scale;
+      *reinterpret_cast<f32x4*>(a.dvb + at) = dv[t];
+    }
   }
 }
 
-// ---- work order of the row kernels: the blocks by decreasing anchor (ties by index), so that
-// the work-groups with the longest contexts start first and the short ones fill the tail.
-// Thread i counts the blocks that go before block i. ----
+// ---- work order of the row and context-key kernels: the blocks by decreasing anchor (ties by
+// index), so that the work-groups with the longest contexts start first, the blocks of one
+// work-group are of nearly equal length, and a chunk's blocks that see a key come first.  Thread
+// (i, part) counts the blocks of its sixteenth that go before block i. ----
 __global__ __launch_bounds__(256) void k_anchor_order(const int32_t* __restrict__ anchors, int n, int T,
                                                       int* __restrict__ order) {
-  __shared__ int part[4][64];
-  // lane l of wave q: block i = 64 * blockIdx.x + l against the q-th quarter of the blocks; the
-  // quarter's anchors are the same for the whole wave (scalar loads)
-  const int l = threadIdx.x & 63, q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int i = blockIdx.x * 64 + l;
+  __shared__ int cnt[16][17];
+  const int l = threadIdx.x & 15, part = threadIdx.x >> 4;
+  const int i = blockIdx.x * 16 + l;
   const int ai = i < n ? min(max(anchors[i], 0), T) : 0;
-  const int per = (n + 3) / 4, jb = q * per, je = min(n, jb + per);
   int rank = 0;
 #pragma unroll 8
-  for (int j = jb; j < je; ++j) {
+  for (int j = part; j < n; j += 16) {
     const int aj = min(max(anchors[j], 0), T);
     rank += (aj > ai || (aj == ai && j < i)) ? 1 : 0;
   }
-  part[q][l] = rank;
+  cnt[l][part] = rank;
   __syncthreads();
-  if (q == 0 && i < n) order[part[0][l] + part[1][l] + part[2][l] + part[3][l]] = i;
+  if (part == 0 && i < n) {
+    for (int p = 1; p < 16; ++p) rank += cnt[l][p];
+    order[rank] = i;
+  }
 }
 
-// ---- forward and dQ: work-group (block i, KV head g), blocks taken in the order above; its 4 waves take the 16-row query
-// tiles w, w + 4 (TPW tiles each).  Key tiles of 32 (the context before the anchor, then the
-// block's own keys) are shared through LDS, double-buffered: LDS-direct loads fill the next
-// tile while the current one goes through the matrix cores.  Per stage: K rows (and for dQ
-// V rows), 16-byte pieces of key k in slot k*(HD/8) + (c ^ rsw(k)); and the transposed tile
-// (V^T, or K^T for dQ), piece c (8 keys) of dim row d in slot d*4 + (c ^ tsw(d)).  Keys a
-// block does not see are read from a visible row and masked in the scores.
-template <int HD, bool DQ, int TPW>
-__global__ __launch_bounds__(kTrT) void k_aatt_rows(AttnT a) {
-  constexpr int PK = HD / 8;                   // 16-byte pieces of a key row
-  constexpr int KP = 32 * PK, TP = HD * 4;     // pieces of a key-row tile / of a transposed tile
-  constexpr int NP = (DQ ? 2 * KP : KP) + TP;  // pieces per stage
-  static_assert(NP % 64 == 0, "whole wave loads");
-  __shared__ u32x4 lds[2][NP];
+// ---- forward and dQ.  A wave takes 32 query rows of a block (its B operand, in registers) through
+// 32-key tiles: the context before the anchor, then the block's own keys.  A block is WPB
+// waves; the 4 waves of a work-group are NB = 4 / WPB blocks that follow each other in the work
+// order (KS = 1), or one block whose key tiles go to KS wave groups in turn, merged at the end.
+// The K and V tiles go through two LDS buffers of KS tiles each, one barrier per buffer.
+// Bound by instruction issue: per tile and wave 16 (dQ: 24) 32 x 32 x 16 products of 32 clocks and about
+// 110 vector instructions, which share the issue slots of two waves per SIMD.  512 blocks of 4 x 16
+// rows, T = 3,072, 8 KV heads x 128: 330 -> 255 us forward, 440 -> 325 us dQ against 16-row waves
+// on 16 x 16 x 32 products.
+template <int HD, bool DQ, int WPB, int KS>
+__global__ __launch_bounds__(kTrT, KS == 1 ? 2 : 1) void k_aatt_rows(AttnT a) {
+  constexpr int NB = KS > 1 ? 1 : 4 / WPB;
+  constexpr int NK = HD / 16, ND = HD / 32;  // k-steps and dim tiles of a head
+  constexpr int TB = kTileBytes<HD>;
+  constexpr int PW = NK * KS / 4;            // K (and V) fragments per wave and step
+  constexpr int SB = 2 * KS * TB;            // bytes of a buffer: KS K tiles, KS V tiles
+  constexpr int NOWN = (NB + 1) / 2;         // tiles of own keys: 16 rows of each of two blocks (past B key B - 1)
+  __shared__ __attribute__((aligned(1024))) char lds[2 * SB];
+  __shared__ __attribute__((aligned(1024))) char own[2 * NOWN * TB];  // K tiles, V tiles
   const AttnShapeT& s = a.s;
-  const int i = a.order[blockIdx.x], g = blockIdx.y;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int col = lane & 15, q4 = lane >> 4;
-  const int QT = (s.R + 15) / 16;
-  const int anchor = min(max(a.anchors[i], 0), s.T);
-  const int nct = (anchor + 31) / 32;
+  int g, unit;
+  unit_head(blockIdx.x, s.n_kv, unit, g);
+  if (unit * NB >= s.n_blocks) return;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n32 = lane & 31, h = lane >> 5;
+  const int wr = w % WPB, grp = w / WPB;
+  const int ks_id = KS > 1 ? grp : 0, nb = KS > 1 ? 0 : grp;
+  int blk[NB], nctx = 0;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    blk[b] = a.order[min(unit * NB + b, s.n_blocks - 1)];
+    nctx = max(nctx, (min(max(a.anchors[blk[b]], 0), s.T) + 31) / 32);
+  }
+  const bool active = grp < (KS > 1 ? KS : NB) && unit * NB + nb < s.n_blocks && 32 * wr < s.R;
+  const int i = a.order[min(unit * NB + (active ? nb : 0), s.n_blocks - 1)];
+  const int anchor = active ? min(max(a.anchors[i], 0), s.T) : 0;
+  // steps of the work-group, and of this wave
+  const int nstep = (nctx + KS - 1) / KS, mine = max(0, ((anchor + 31) / 32 - ks_id + KS - 1) / KS);
   const float sl2 = a.scale * 1.4426950408889634f;
   const u32x4 z4 = {0u, 0u, 0u, 0u};
-  const uint16_t* tsrc_c = DQ ? a.kct : a.vct;
-  const uint16_t* tsrc_b = DQ ? a.kbt : a.vbt;
-
-  // LDS-direct loads of key tile kt into buffer bi.  Each region (K rows, V rows for dQ, the
-  // transposed tile) is RW wave-loads; wave w issues loads w, w + 4, ... of each, from a
-  // per-tile base plus a per-lane offset fixed for the whole kernel.  Keys past T (the last
-  // context tile) and block keys past B read row 0; their scores are masked.
-  constexpr int RW = HD / 16, PW = RW / 4;
-  int kk[PW], cofs[PW], rofs_b[PW], tofs_c[PW], tofs_b[PW];
+  // A step's K and V tiles into registers (past the last tile the last again, rows past T repeat the
+  // last one: masked), and from there into a buffer.  A wave-load is 16 rows x 4 pieces: 64-byte
+  // segments from memory, and to LDS every 16 lanes write 256 different bytes modulo the bank cycle.
+  const int lr = lane >> 2, lc = lane & 3;
+  u32x4 nk[PW], nv[PW];
+  auto fetch = [&](int step) {
 #pragma unroll
-  for (int t = 0; t < PW; ++t) {
-    const int sl = (w + 4 * t) * 64 + lane;
-    const int k = sl / PK, d = sl / 4;
-    kk[t] = k;
-    cofs[t] = ((sl % PK) ^ rsw<PK>(k)) * 8;
-    rofs_b[t] = (k < s.B ? k : 0) * s.n_kv * HD + cofs[t];
-    const int ct = ((sl % 4) ^ tsw(d)) * 8;
-    tofs_c[t] = d * s.Tp + ct;
-    tofs_b[t] = d * s.Mp + ct;
-  }
-  // (source pointers through locals: an array element inside the builtin's argument left the
-  // host-side launch stub undefined)
-  auto issue = [&](int bi, int t, const uint16_t* sk, const uint16_t* sv, const uint16_t* stt) {
+    for (int t = 0; t < PW; ++t) {
+      const int ins = w + 4 * t;
+      const int row = min(step * KS + ins / NK, nctx - 1) * 32 + 16 * (ins & 1) + lr;
+      const long at = ((long)min(row, s.T - 1) * s.n_kv + g) * HD + (ins % NK >> 1) * 32 + lc * 8;
+      nk[t] = ld16(a.kc + at);
+      nv[t] = ld16(a.vc + at);
+    }
+  };
+  auto slot_of = [&](int ins) { return ins / NK * TB + piece_at(16 * (ins & 1) + lr, (ins % NK >> 1) * 4 + lc); };
+  auto store = [&](int bi) {
+#pragma unroll
+    for (int t = 0; t < PW; ++t) {
+      char* dst = lds + bi * SB + slot_of(w + 4 * t);
+      *reinterpret_cast<u32x4*>(dst) = nk[t];
+      *reinterpret_cast<u32x4*>(dst + KS * TB) = nv[t];
+    }
+  };
+#pragma unroll
+  for (int t = 0; t < NOWN * NK / 4; ++t) {
     const int ins = w + 4 * t;
-    __builtin_amdgcn_global_load_lds(sk, (LDSP char*)(char*)&lds[bi][ins * 64], 16, 0, 0);
-    if constexpr (DQ) __builtin_amdgcn_global_load_lds(sv, (LDSP char*)(char*)&lds[bi][(RW + ins) * 64], 16, 0, 0);
-    __builtin_amdgcn_global_load_lds(stt, (LDSP char*)(char*)&lds[bi][((DQ ? 2 : 1) * RW + ins) * 64], 16, 0, 0);
-  };
-  auto stage = [&](int kt, int bi) {
-    if (kt == nct) {  // the block's own keys
-      const long r0 = ((long)i * s.B * s.n_kv + g) * HD;
-      const uint16_t* bt = tsrc_b + (long)g * HD * s.Mp + (long)i * 32;
-#pragma unroll
-      for (int t = 0; t < PW; ++t) {
-        const int ro = rofs_b[t], to = tofs_b[t];
-        issue(bi, t, a.kb + r0 + ro, a.vb + r0 + ro, bt + to);
-      }
-    } else {
-      const long r0 = ((long)kt * 32 * s.n_kv + g) * HD;
-      const uint16_t* bt = tsrc_c + (long)g * HD * s.Tp + (long)kt * 32;
-      const bool tail = (kt + 1) * 32 > s.T;
-#pragma unroll
-      for (int t = 0; t < PW; ++t) {
-        long ro = r0 + (long)kk[t] * s.n_kv * HD + cofs[t];
-        if (tail && kt * 32 + kk[t] >= s.T) ro = (long)g * HD + cofs[t];  // key 0
-        const int to = tofs_c[t];
-        issue(bi, t, a.kc + ro, a.vc + ro, bt + to);
-      }
-    }
-  };
+    constexpr int kLast = NB - 1;
+    const int b0 = blk[min(2 * (4 * t / NK), kLast)], b1 = blk[min(2 * (4 * t / NK) + 1, kLast)];
+    const int row = (ins & 1 ? b1 : b0) * s.B + min(lr, s.B - 1);
+    const long at = ((long)row * s.n_kv + g) * HD + (ins % NK >> 1) * 32 + lc * 8;
+    *reinterpret_cast<u32x4*>(own + slot_of(ins)) = ld16(a.kb + at);
+    *reinterpret_cast<u32x4*>(own + NOWN * TB + slot_of(ins)) = ld16(a.vb + at);
+  }
+  if (nctx > 0) {
+    fetch(0);
+    store(0);
+    fetch(1);
+  }
+  int fo[2], off[2];
+  frag_offsets(lane, fo);
+  tr_offsets(lane, off);
 
-  // per query tile of this wave: Q (and dO) fragments, softmax state, accumulators
-  u32x4 qf[TPW][HD / 32], df[TPW][HD / 32];
-  float m[TPW], l[TPW], lse2[TPW], dr[TPW];
-  f32x4 o[TPW][HD / 16];
+  // this wave's rows: Q (and dO) operands, softmax state or row statistics, accumulators
+  const int r = 32 * wr + n32;
+  const bool rv = active && r < s.R;
+  const long rh = rv ? (long)(i * s.B + r % s.B) * s.n_q + g * s.G + r / s.B : 0;
+  u32x4 qf[NK], df[DQ ? NK : 1];
 #pragma unroll
-  for (int tt = 0; tt < TPW; ++tt) {
-    const int r = 16 * (w + 4 * tt) + col;
-    const bool rv = r < s.R;
-    const int h = g * s.G + (rv ? r / s.B : 0), b = rv ? r % s.B : 0;
-    const long qrow = ((long)(i * s.B + b) * s.n_q + h) * HD;
-#pragma unroll
-    for (int ks = 0; ks < HD / 32; ++ks) {
-      qf[tt][ks] = rv ? ld16(a.q + qrow + ks * 32 + 8 * q4) : z4;
-      if constexpr (DQ) df[tt][ks] = rv ? ld16(a.dob + qrow + ks * 32 + 8 * q4) : z4;
-    }
-    m[tt] = -1e30f;  // finite: 2^(-inf - m) = 0 for masked keys before any visible one
-    l[tt] = 0.f;
-    lse2[tt] = dr[tt] = 0.f;
+  for (int k = 0; k < NK; ++k) {
     if constexpr (DQ) {
-      lse2[tt] = rv ? a.lse[(long)(i * s.B + b) * s.n_q + h] * 1.4426950408889634f : 0.f;
-      dr[tt] = rv ? a.dsum[(long)(i * s.B + b) * s.n_q + h] : 0.f;
-    }
-#pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt) o[tt][dt] = zero4();
-  }
-
-  const char* L0 = reinterpret_cast<const char*>(&lds[0][0]);
-  stage(0, 0);
-  wait_vm();
-  __syncthreads();
-  // one key tile; the buffer index is a compile-time constant (the loop below runs tiles in
-  // pairs), so every LDS read takes its buffer offset as an immediate
-  auto tile = [&](int kt, auto BI) {
-    constexpr int bi = decltype(BI)::value;
-    if (kt < nct) stage(kt + 1, bi ^ 1);
-    const bool blk = kt == nct;
-    const char* Lb = L0 + bi * NP * 16;
-    // A-operand rows of this lane: keys 16 x + col
-    u32x4 ka[2][HD / 32], va[2][HD / 32];
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-      for (int ks = 0; ks < HD / 32; ++ks) {
-        const int k = 16 * x + col;
-        const int sl = k * PK + ((ks * 4 + q4) ^ rsw<PK>(k));
-        ka[x][ks] = *reinterpret_cast<const u32x4*>(Lb + sl * 16);
-        if constexpr (DQ) va[x][ks] = *reinterpret_cast<const u32x4*>(Lb + (KP + sl) * 16);
-      }
-    // every key of the tile visible (all context tiles but the last): no masking
-    const bool full = !blk && (kt + 1) * 32 <= anchor;
-    // transposed operand pieces of this lane (dims 16 dt + col), read once for all its tiles
-    u32x4 tpair[HD / 16];
-#pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt) {
-      const int d = 16 * dt + col;
-      const int base = (DQ ? 2 * KP : KP) + d * 4;
-      const int c0 = (q4 >> 1) ^ tsw(d), c1 = (2 + (q4 >> 1)) ^ tsw(d);
-      const u32x2 lo = *reinterpret_cast<const u32x2*>(Lb + (base + c0) * 16 + (q4 & 1) * 8);
-      const u32x2 hi = *reinterpret_cast<const u32x2*>(Lb + (base + c1) * 16 + (q4 & 1) * 8);
-      tpair[dt] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-    }
-#pragma unroll
-    for (int tt = 0; tt < TPW; ++tt) {
-      if (w + 4 * tt >= QT) continue;
-      f32x4 s0 = zero4(), s1 = zero4(), p0 = zero4(), p1 = zero4();
-#pragma unroll
-      for (int ks = 0; ks < HD / 32; ++ks) {
-        s0 = mfma(ka[0][ks], qf[tt][ks], s0);
-        s1 = mfma(ka[1][ks], qf[tt][ks], s1);
-        if constexpr (DQ) {
-          p0 = mfma(va[0][ks], df[tt][ks], p0);  // dP^T
-          p1 = mfma(va[1][ks], df[tt][ks], p1);
-        }
-      }
-      // raw scores of this lane (keys 4 q4 + e and 16 + 4 q4 + e), -inf where masked; the
-      // log2-domain scale sl2 > 0 goes into each exponent as one fma
-      float x0[4], x1[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        x0[e] = s0[e];
-        x1[e] = s1[e];
-      }
-      if (!full) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int j0 = 4 * q4 + e, j1 = 16 + 4 * q4 + e;
-          if (!(blk ? j0 < s.B : kt * 32 + j0 < anchor)) x0[e] = -INFINITY;
-          if (!(blk ? j1 < s.B : kt * 32 + j1 < anchor)) x1[e] = -INFINITY;
-        }
-      }
-      u32x4 pb;
-      if constexpr (!DQ) {
-        // the running maximum moves only when the tile's maximum exceeds it by more than 8
-        // (so unnormalised probabilities stay below 2^8); the rescale of O and l then runs
-        // for the whole wave, with factor 1 on rows that did not move
-        float tm = fmaxf(fmaxf(x0[0], x1[0]), fmaxf(x0[1], x1[1]));
-        tm = fmaxf(tm, fmaxf(fmaxf(x0[2], x1[2]), fmaxf(x0[3], x1[3])));
-        tm = fmaxf(tm, __shfl_xor(tm, 16));
-        tm = fmaxf(tm, __shfl_xor(tm, 32));
-        tm *= sl2;  // max of the log2-domain scores (scaling by sl2 > 0 keeps the maximum)
-        const bool grow = tm > m[tt] + 8.f;
-        if (__builtin_amdgcn_ballot_w64(grow) != 0) {
-          const float mn = grow ? tm : m[tt];
-          const float corr = ex2(m[tt] - mn);
-          l[tt] *= corr;
-#pragma unroll
-          for (int dt = 0; dt < HD / 16; ++dt) o[tt][dt] *= corr;
-          m[tt] = mn;
-        }
-        float ps = 0.f;
-        f32x4 e0, e1;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          e0[e] = ex2(fmaf(x0[e], sl2, -m[tt]));
-          e1[e] = ex2(fmaf(x1[e], sl2, -m[tt]));
-          ps += e0[e] + e1[e];
-        }
-        l[tt] += ps;
-        pb = pack_bf8(e0, e1);
-      } else {
-        f32x4 d0, d1;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          d0[e] = ex2(fmaf(x0[e], sl2, -lse2[tt])) * (p0[e] - dr[tt]);
-          d1[e] = ex2(fmaf(x1[e], sl2, -lse2[tt])) * (p1[e] - dr[tt]);
-        }
-        pb = pack_bf8(d0, d1);
-      }
-      // O^T += V^T P^T (forward) or dQ^T += K^T dS^T
-#pragma unroll
-      for (int dt = 0; dt < HD / 16; ++dt) o[tt][dt] = mfma(tpair[dt], pb, o[tt][dt]);
-    }
-    wait_vm();
-    __syncthreads();
-  };
-  for (int kt = 0; kt <= nct; kt += 2) {
-    tile(kt, std::integral_constant<int, 0>{});
-    if (kt + 1 <= nct) tile(kt + 1, std::integral_constant<int, 1>{});
-  }
-#pragma unroll
-  for (int tt = 0; tt < TPW; ++tt) {
-    const int r = 16 * (w + 4 * tt) + col;
-    if (w + 4 * tt >= QT || r >= s.R) continue;
-    const int h = g * s.G + r / s.B, b = r % s.B;
-    const long qrow = ((long)(i * s.B + b) * s.n_q + h) * HD;
-    float out_scale;
-    if constexpr (!DQ) {
-      float lt = l[tt];
-      lt += __shfl_xor(lt, 16);
-      lt += __shfl_xor(lt, 32);
-      out_scale = 1.f / lt;
-      if (q4 == 0) a.lse[(long)(i * s.B + b) * s.n_q + h] = (m[tt] + log2f(lt)) * 0.6931471805599453f;
+      const long at = ((long)(g * s.n_blocks + i) * (s.Rp / 32) + (active ? wr : 0)) * TB + k * 1024 + fo[k & 1];
+      qf[k] = ld16b(reinterpret_cast<const char*>(a.qf) + at);
+      df[k] = ld16b(reinterpret_cast<const char*>(a.df) + at);
     } else {
-      out_scale = a.scale;
-    }
-    float* dst = (DQ ? a.dq : a.out) + qrow;
-#pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt) *reinterpret_cast<f32x4*>(dst + 16 * dt + 4 * q4) = o[tt][dt] * out_scale;
-  }
-}
-
-// ---- block-key dK, dV: work-group (block ib, KV head g); wave w takes the block's 32-row
-// pairs w, w + 4, ... and the 4 waves' sums are added in wave order ----
-template <int HD>
-__global__ __launch_bounds__(kTrT) void k_aatt_kvb(AttnT a) {
-  constexpr int NX = kMaxBlockKeys / 16;  // 16-key tiles of a block's keys (B <= kMaxBlockKeys)
-  const AttnShapeT& s = a.s;
-  const int g = blockIdx.y;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int col = lane & 15, q4 = lane >> 4;
-  const float sl2 = a.scale * 1.4426950408889634f;
-  const int NP = s.Rp / 32;  // 32-row pairs of a (block, group)
-  const u32x4 z4 = {0u, 0u, 0u, 0u};
-  const int ib = blockIdx.x;
-  f32x4 dk[HD / 16][NX], dv[HD / 16][NX];
-#pragma unroll
-  for (int dt = 0; dt < HD / 16; ++dt)
-#pragma unroll
-    for (int x = 0; x < NX; ++x) dk[dt][x] = dv[dt][x] = zero4();
-  // B-operand rows (keys) of this lane: key 16x + col of the tile
-  u32x4 kf[NX][HD / 32], vf[NX][HD / 32];
-#pragma unroll
-  for (int x = 0; x < NX; ++x) {
-    const int j = 16 * x + col;
-    const bool ok = j < s.B;
-    const long row = ok ? ((long)(ib * s.B + j) * s.n_kv + g) * HD : 0;
-    const uint16_t* kp = a.kb + row;
-    const uint16_t* vp = a.vb + row;
-#pragma unroll
-    for (int ks = 0; ks < HD / 32; ++ks) {
-      kf[x][ks] = ok ? ld16(kp + ks * 32 + 8 * q4) : z4;
-      vf[x][ks] = ok ? ld16(vp + ks * 32 + 8 * q4) : z4;
+      qf[k] = rv ? ld16(a.q + rh * HD + k * 16 + 8 * h) : z4;
     }
   }
-  const int i = ib;
-  for (int pr = w; pr < NP; pr += 4) {
-    // S = Q K^T and dP = dO V^T for rows 32 pr + 16 y + (4 q4 + e) (y = 0, 1), keys 16x + col
-    f32x4 sc[2][NX], dp[2][NX];
-#pragma unroll
-    for (int y = 0; y < 2; ++y)
-#pragma unroll
-      for (int x = 0; x < NX; ++x) sc[y][x] = dp[y][x] = zero4();
-#pragma unroll
-    for (int y = 0; y < 2; ++y) {
-      const int r = 32 * pr + 16 * y + col;  // A row of this lane
-      const bool rv = r < s.R;
-      const long qrow = rv ? ((long)(i * s.B + r % s.B) * s.n_q + g * s.G + r / s.B) * HD : 0;
-#pragma unroll
-      for (int ks = 0; ks < HD / 32; ++ks) {
-        const u32x4 qa = rv ? ld16(a.q + qrow + ks * 32 + 8 * q4) : z4;
-        const u32x4 da = rv ? ld16(a.dob + qrow + ks * 32 + 8 * q4) : z4;
-#pragma unroll
-        for (int x = 0; x < NX; ++x) {
-          sc[y][x] = mfma(qa, kf[x][ks], sc[y][x]);
-          dp[y][x] = mfma(da, vf[x][ks], dp[y][x]);
-        }
-      }
-    }
-    // P and dS at this lane's values: row 32 pr + 16 y + 4 q4 + e, key 16 x + col
-    f32x4 P[2][NX], dS[2][NX];
-#pragma unroll
-    for (int y = 0; y < 2; ++y) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = 32 * pr + 16 * y + 4 * q4 + e;
-        const bool rv = r < s.R;
-        const long rh = rv ? (long)(i * s.B + r % s.B) * s.n_q + g * s.G + r / s.B : 0;
-        const float lse2 = rv ? a.lse[rh] * 1.4426950408889634f : 0.f;
-        const float dr = rv ? a.dsum[rh] : 0.f;
-#pragma unroll
-        for (int x = 0; x < NX; ++x) {
-          const int j = 16 * x + col;
-          const bool ok = rv && j < s.B;
-          const float p = ok ? ex2(fmaf(sc[y][x][e], sl2, -lse2)) : 0.f;
-          P[y][x][e] = p;
-          dS[y][x][e] = p * (dp[y][x][e] - dr);
-        }
-      }
-    }
-    // dV^T += dO^T P, dK^T += Q^T dS: A rows = dims d = 16 dt + col, k = the pair's 32 rows
-    const long tb = ((long)g * s.n_blocks + i) * HD * s.Rp + 32 * pr + 4 * q4;
-#pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt) {
-      const long off = tb + (long)(16 * dt + col) * s.Rp;
-      const u32x4 doa = ld_pair(a.dot + off);
-      const u32x4 qa = ld_pair(a.qt + off);
-#pragma unroll
-      for (int x = 0; x < NX; ++x) {
-        dv[dt][x] = mfma(doa, pack_bf8(P[0][x], P[1][x]), dv[dt][x]);
-        dk[dt][x] = mfma(qa, pack_bf8(dS[0][x], dS[1][x]), dk[dt][x]);
-      }
-    }
+  float m = -1e30f, l = 0.f;  // m finite: 2^(-inf - m) = 0 for masked keys before any visible one
+  float lse2 = 0.f, nd = 0.f;
+  if constexpr (DQ) {
+    lse2 = rv ? a.lse[rh] * 1.4426950408889634f : 0.f;
+    nd = rv ? a.st[(((long)g * s.n_blocks + i) * 2 + 1) * s.Rp + r] : 0.f;
   }
-  // sum the 4 waves' tiles in wave order through LDS, 8 tiles per round
-  __shared__ f32x4 red[3][8][64];
-  constexpr int NT = HD / 16 * NX * 2;  // tiles per wave (dK, dV)
-  static_assert(NT % 8 == 0, "8 tiles per round");
+  f32x16 o[ND];
 #pragma unroll
-  for (int r0 = 0; r0 < NT; r0 += 8) {
-    if (w > 0) {
+  for (int dt = 0; dt < ND; ++dt) o[dt] = splat16(0.f);
+  // a tile's scores: raw ones of this lane's row against keys 8 (e / 4) + 4 h + e mod 4 (the log2-domain
+  // scale sl2 > 0 goes into each exponent as one fma), and dP for dQ
+  f32x16 sc, dp;
+  auto scores = [&](const char* kt, const char* vt) {
+    sc = splat16(0.f);
+    dp = splat16(nd);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int tI = r0 + u, kind = tI / (HD / 16 * NX), rem = tI % (HD / 16 * NX);
-        red[w - 1][u][lane] = kind == 0 ? dk[rem / NX][rem % NX] : dv[rem / NX][rem % NX];
+    for (int k = 0; k < NK; ++k) {
+      sc = mfma32(ld16b(kt + k * 1024 + fo[k & 1]), qf[k], sc);
+      if constexpr (DQ) dp = mfma32(ld16b(vt + k * 1024 + fo[k & 1]), df[k], dp);
+    }
+  };
+  // only the tile's keys k0 .. k1 - 1 are visible
+  auto mask = [&](int k0, int k1) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int key = 8 * (e >> 2) + 4 * h + (e & 3);
+      if (key < k0 || key >= k1) sc[e] = -INFINITY;
+    }
+  };
+  // scores -> P (forward; O and l follow the running maximum) or dS
+  f32x16 p;
+  auto weigh = [&]() {
+    if constexpr (!DQ) {
+      // the running maximum moves only when the tile's maximum exceeds it by more than 8 (so
+      // unnormalised probabilities stay below 2^8); the rescale of O and l then runs for the
+      // whole wave, with factor 1 on rows that did not move
+      float tm = sc[0];
+#pragma unroll
+      for (int e = 1; e < 16; ++e) tm = fmaxf(tm, sc[e]);
+      tm = fmaxf(tm, __shfl_xor(tm, 32));
+      tm *= sl2;  // max of the log2-domain scores (scaling by sl2 > 0 keeps the maximum)
+      const bool grow = tm > m + 8.f;
+      if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+        const float mn = grow ? tm : m;
+        const float corr = ex2(m - mn);
+        l *= corr;
+#pragma unroll
+        for (int dt = 0; dt < ND; ++dt) o[dt] *= corr;
+        m = mn;
       }
+      float ps = 0.f;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        p[e] = ex2(fmaf(sc[e], sl2, -m));
+        ps += p[e];
+      }
+      l += ps;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) p[e] = ex2(fmaf(sc[e], sl2, -lse2)) * dp[e];
+    }
+  };
+  // O^T += V^T P^T (forward) or dQ^T += K^T dS^T, over keys 16 ks .. 16 ks + 15 of the tile
+  auto gather = [&](const char* lt, int ks) {
+    const u32x4 pb = pack_half(p, ks);
+#pragma unroll
+    for (int dt = 0; dt < ND; ++dt) o[dt] = mfma32(ld_tr_op(lt, off, ks, dt), pb, o[dt]);
+  };
+  // one step; the buffer index is a compile-time constant (steps run in pairs)
+  auto step = [&](int st, auto BI) {
+    constexpr int bi = decltype(BI)::value;
+    lds_barrier();
+    store(bi ^ 1);  // step st + 1's tiles
+    fetch(st + 2);
+    if (st >= mine) return;  // the work-group's other waves have longer contexts
+    const char* kt = lds + bi * SB + ks_id * TB;
+    const char* vt = kt + KS * TB;
+    scores(kt, vt);
+    const int keys = anchor - (st * KS + ks_id) * 32;
+    if (keys < 32) mask(0, keys);
+    weigh();
+    gather(DQ ? kt : vt, 0);
+    gather(DQ ? kt : vt, 1);
+  };
+  for (int st = 0; st < nstep; st += 2) {
+    step(st, std::integral_constant<int, 0>{});
+    if (st + 1 < nstep) step(st + 1, std::integral_constant<int, 1>{});
+  }
+  if (nstep == 0) lds_barrier();
+  if (active && ks_id == 0) {  // (the other block's half of the tile takes no part, whatever it holds)
+    const char* kt = own + nb / 2 * TB;
+    const char* vt = kt + NOWN * TB;
+    const int half = nb & 1;
+    scores(kt, vt);
+    mask(16 * half, 16 * half + s.B);
+    weigh();
+    if (half == 0) gather(DQ ? kt : vt, 0);
+    else gather(DQ ? kt : vt, 1);
+  }
+  if constexpr (KS > 1) {
+    // merge the wave groups in order: 4-dim pieces of O [group - 1][WPB][piece][lane], (m, l)
+    constexpr int NP = ND * 4;
+    f32x4* mo = reinterpret_cast<f32x4*>(lds);
+    float2* ml = reinterpret_cast<float2*>(lds + SB);
+    static_assert((KS - 1) * WPB * NP * 1024 <= SB, "merge area");
+    __syncthreads();
+    if (grp > 0) {
+#pragma unroll
+      for (int x = 0; x < NP; ++x)
+        mo[(((grp - 1) * WPB + wr) * NP + x) * 64 + lane] =
+            f32x4{o[x / 4][4 * (x % 4)], o[x / 4][4 * (x % 4) + 1], o[x / 4][4 * (x % 4) + 2], o[x / 4][4 * (x % 4) + 3]};
+      ml[((grp - 1) * WPB + wr) * 64 + lane] = make_float2(m, l);
     }
     __syncthreads();
-    if (w == 0) {
+    if (grp > 0) return;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int tI = r0 + u, kind = tI / (HD / 16 * NX), rem = tI % (HD / 16 * NX);
-        const int dt = rem / NX, x = rem % NX;
-        f32x4 v = kind == 0 ? dk[dt][x] : dv[dt][x];
-        v += red[0][u][lane];
-        v += red[1][u][lane];
-        v += red[2][u][lane];
-        if (kind == 0) v *= a.scale;
-        // tile (dims 16 dt + 4 q4 + e, key 16 x + col)
-        const int j = 16 * x + col;
-        if (j < s.B) {
-          const long row = (long)(ib * s.B + j);
-          float* dst = (kind == 0 ? a.dkb : a.dvb) + (row * s.n_kv + g) * HD + 16 * dt + 4 * q4;
-          *reinterpret_cast<f32x4*>(dst) = v;
+    for (int y = 0; y < KS - 1; ++y) {
+      float ca = 1.f, cb = 1.f;
+      if constexpr (!DQ) {
+        const float2 v = ml[(y * WPB + wr) * 64 + lane];
+        const float mn = fmaxf(m, v.x);
+        ca = ex2(m - mn);
+        cb = ex2(v.x - mn);
+        l = l * ca + v.y * cb;
+        m = mn;
+      }
+#pragma unroll
+      for (int x = 0; x < NP; ++x) {
+        const f32x4 v = mo[((y * WPB + wr) * NP + x) * 64 + lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float t = o[x / 4][4 * (x % 4) + e];
+          o[x / 4][4 * (x % 4) + e] = DQ ? t + v[e] : t * ca + v[e] * cb;
         }
       }
     }
-    __syncthreads();
   }
+  float out_scale = a.scale;
+  if constexpr (!DQ) {
+    l += __shfl_xor(l, 32);
+    out_scale = 1.f / l;
+    if (rv && h == 0) a.lse[rh] = (m + log2f(l)) * 0.6931471805599453f;
+  }
+  if (!rv) return;
+  float* dst = (DQ ? a.dq : a.out) + rh * HD + 4 * h;
+#pragma unroll
+  for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+      *reinterpret_cast<f32x4*>(dst + 32 * dt + 8 * x) =
+          f32x4{o[dt][4 * x], o[dt][4 * x + 1], o[dt][4 * x + 2], o[dt][4 * x + 3]} * out_scale;
 }
 
-// ---- context dK, dV: work-group (64-key tile kt, KV head g, chunk z of 64 blocks); wave w
-// owns keys 64 kt + 16 w + (0..15) (its K and V rows held as operand fragments).  The
-// waves walk the chunk's (block, 32-row pair) units together: each unit's Q rows, dO rows,
-// Q^T and dO^T tiles (from the grouped copies) go through swizzled LDS, double-buffered with
-// LDS-direct loads one unit ahead; per unit a wave forms S = Q K^T and dP = dO V^T for its keys
-// and accumulates dV^T += dO^T P and dK^T += Q^T dS.  Writes this chunk's partial dK, dV.
-// Work-groups are numbered so that the 8 XCDs (which take work-groups round-robin) each run
-// whole (group, chunk) sets, whose units then stay in that XCD's L2. ----
+// ---- context dK, dV: work-group (128-key tile kt, KV head g, chunk z); wave w owns keys 128 kt + 32 w
+// + (0..31): their K and V rows are its B operands, dK^T and dV^T its accumulators, all in
+// registers.  The waves walk the (block, 32-row tile) units of the chunk's blocks that see a key of
+// the tile (the first nvis in the work order): per unit a wave forms S = Q K^T and dP = dO V^T (the
+// row statistics are their initial values) and adds dO^T P and Q^T dS.  The units' tiles and
+// statistics go through three LDS buffers, one barrier per unit.  The scores of one unit are formed
+// between the gradient products of the unit before, so that the exponentials have products beside
+// them; one wave per SIMD, with 512 registers.
+// Writes this chunk's partial dK, dV.  512 blocks, T = 3,072: 658 -> 500 us against 16-key waves with
+// transposed copies of Q and dO; with two waves per SIMD and 256 registers 650.  Work-groups are numbered so that each of the 8 XCDs (which take
+// work-groups round-robin) runs whole chunks, all heads of a key tile together (see unit_head).
+constexpr int kKvcKeys = 128;
 template <int HD>
-__global__ __launch_bounds__(kTrT, 2) void k_aatt_kvc(AttnT a) {
-  constexpr int PK = HD / 8;                  // 16-byte pieces of a row
-  constexpr int RW = HD / 16;                 // wave-loads of one 32-row (or transposed) tile
-  constexpr int PW = RW / 4;                  // of them per wave
-  constexpr int NPc = 4 * RW * 64;            // Q, dO, Q^T, dO^T
-  __shared__ u32x4 lds[2][NPc];
+__global__ __launch_bounds__(kTrT, 1) void k_aatt_kvc(AttnT a) {
+  constexpr int NK = HD / 16, ND = HD / 32;
+  constexpr int TB = kTileBytes<HD>, PW = NK / 4;
+  constexpr int SB = 2 * TB + 256;  // a buffer: Q tile, dO tile, the rows' 2 x 32 statistics
+  __shared__ __attribute__((aligned(1024))) char lds[3 * SB];
   const AttnShapeT& s = a.s;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int col = lane & 15, q4 = lane >> 4;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n32 = lane & 31, h = lane >> 5;
   // work-group -> (kt, g, z)
   const int nkt = gridDim.x;
   const int N = nkt * gridDim.y * gridDim.z;
   const int n = blockIdx.x + nkt * (blockIdx.y + gridDim.y * blockIdx.z);
   const int xq = N / 8, xr = N % 8, x8 = n % 8;
   const int lg = x8 * xq + min(x8, xr) + n / 8;
-  const int kt = lg % nkt, g = (lg / nkt) % s.n_kv, z = lg / (nkt * s.n_kv);
+  const int g = lg % s.n_kv, kt = (lg / s.n_kv) % nkt, z = lg / (nkt * s.n_kv);
 
   const float sl2 = a.scale * 1.4426950408889634f;
-  const u32x4 z4 = {0u, 0u, 0u, 0u};
   const int NPr = s.Rp / 32;
-  const int i0 = z * kChunkBlocks, i1 = min(s.n_blocks, i0 + kChunkBlocks);
-  const int key0 = kt * 64;
-  const int myk = key0 + 16 * w + col;
-  const bool kok = myk < s.T;
-  u32x4 kf[HD / 32], vf[HD / 32];
+  const int key0 = kt * kKvcKeys;
+  // the chunk's blocks, one per lane, by decreasing anchor: those that see a key come first
+  const int pos = z + a.nch * lane;
+  const int myblk = pos < s.n_blocks && lane < kChunkBlocks ? a.order[pos] : 0;
+  const int myanc = pos < s.n_blocks && lane < kChunkBlocks ? min(max(a.anchors[myblk], 0), s.T) : 0;
+  const int nvis = __builtin_popcountll(__builtin_amdgcn_ballot_w64(myanc > key0));
+  const int units = nvis * NPr;
+
+  const int myk = key0 + 32 * w + n32;
+  u32x4 kf[NK], vf[NK];
   {
-    const long row = kok ? ((long)myk * s.n_kv + g) * HD : 0;
+    const long row = ((long)min(myk, s.T - 1) * s.n_kv + g) * HD;
 #pragma unroll
-    for (int ks = 0; ks < HD / 32; ++ks) {
-      kf[ks] = kok ? ld16(a.kc + row + ks * 32 + 8 * q4) : z4;
-      vf[ks] = kok ? ld16(a.vc + row + ks * 32 + 8 * q4) : z4;
+    for (int k = 0; k < NK; ++k) {
+      kf[k] = ld16(a.kc + row + k * 16 + 8 * h);
+      vf[k] = ld16(a.vc + row + k * 16 + 8 * h);
     }
   }
-  f32x4 dk[HD / 16], dv[HD / 16];
+  f32x16 dk[ND], dv[ND];
 #pragma unroll
-  for (int dt = 0; dt < HD / 16; ++dt) dk[dt] = dv[dt] = zero4();
-
-  // this lane's source offsets of its wave-loads t of a tile (same for every unit): row tiles
-  // (32 rows x HD, row-major) and transposed tiles (HD dim rows x Rp)
-  int roff[PW], toff[PW];
-#pragma unroll
-  for (int t = 0; t < PW; ++t) {
-    const int sl = (w + 4 * t) * 64 + lane;
-    const int rr = sl / PK, d = sl / 4;
-    roff[t] = rr * HD + ((sl % PK) ^ rsw<PK>(rr)) * 8;
-    toff[t] = d * s.Rp + ((sl % 4) ^ tsw(d)) * 8;
-  }
-  // the chunk's anchors, one block per lane (a chunk is 64 blocks), and the blocks that see a
-  // key of this tile as a bit mask, walked in block order
-  static_assert(kChunkBlocks == 64, "one block per lane");
-  const int anc = lane < i1 - i0 ? min(max(a.anchors[i0 + lane], 0), s.T) : 0;
-  uint64_t left = __builtin_amdgcn_ballot_w64(anc > key0);
-  auto take_block = [&]() {
-    if (left == 0) return -1;
-    const int j = __builtin_ctzll(left);
-    left &= left - 1;
-    return j;
+  for (int dt = 0; dt < ND; ++dt) dk[dt] = dv[dt] = splat16(0.f);
+  int fo[2], off[2];
+  frag_offsets(lane, fo);
+  tr_offsets(lane, off);
+  // the walk over the units; past the last unit the last again
+  struct Walk {
+    int j = 0, p = 0;
   };
-  auto stage = [&](int j, int pr, int bi) {
-    const int i = i0 + j;
-    const long tile = (long)g * s.n_blocks + i;
-    const uint16_t* rq = a.qr + (tile * s.Rp + 32 * pr) * HD;
-    const uint16_t* rd = a.dor + (tile * s.Rp + 32 * pr) * HD;
-    const uint16_t* tq = a.qt + tile * HD * s.Rp + 32 * pr;
-    const uint16_t* td = a.dot + tile * HD * s.Rp + 32 * pr;
+  auto next = [&](Walk& u) {
+    if (u.p + 1 < NPr) ++u.p;
+    else if (u.j + 1 < nvis) {
+      u.p = 0;
+      ++u.j;
+    }
+  };
+  auto tile_of = [&](const Walk& u) { return ((long)g * s.n_blocks + __builtin_amdgcn_readlane(myblk, u.j)) * NPr + u.p; };
+  Walk wl, wc;  // the unit to load, the unit whose scores come next
+  // a unit's tiles and statistics into registers, and from there into a buffer
+  u32x4 nq[PW], nd[PW];
+  float ns = 0.f;
+  auto fetch = [&]() {
+    const long at = tile_of(wl);
+    const char* bq = reinterpret_cast<const char*>(a.qf) + at * TB + lane * 16;
+    const char* bd = reinterpret_cast<const char*>(a.df) + at * TB + lane * 16;
 #pragma unroll
     for (int t = 0; t < PW; ++t) {
-      const int ins = w + 4 * t;
-      // (source pointers through locals: an array element inside the builtin's argument left
-      // the host-side launch stub of this kernel undefined)
-      const uint16_t* sq = rq + roff[t];
-      const uint16_t* sd = rd + roff[t];
-      const uint16_t* sqt = tq + toff[t];
-      const uint16_t* sdt = td + toff[t];
-      __builtin_amdgcn_global_load_lds(sq, (LDSP char*)(char*)&lds[bi][(0 * RW + ins) * 64], 16, 0, 0);
-      __builtin_amdgcn_global_load_lds(sd, (LDSP char*)(char*)&lds[bi][(1 * RW + ins) * 64], 16, 0, 0);
-      __builtin_amdgcn_global_load_lds(sqt, (LDSP char*)(char*)&lds[bi][(2 * RW + ins) * 64], 16, 0, 0);
-      __builtin_amdgcn_global_load_lds(sdt, (LDSP char*)(char*)&lds[bi][(3 * RW + ins) * 64], 16, 0, 0);
+      nq[t] = ld16b(bq + (w + 4 * t) * 1024);
+      nd[t] = ld16b(bd + (w + 4 * t) * 1024);
     }
+    if (w == 0) ns = a.st[(at - wl.p) * 64 + h * s.Rp + 32 * wl.p + n32];
+    next(wl);
   };
-  // (lse * log2 e, D) of this lane's result rows 32 pr + 16 y + 4 q4 + (0..3)
-  auto row_stats = [&](int j, int pr, f32x4* st4) {
-    const int i = i0 + j;
-    const float2* p = a.st + ((long)g * s.n_blocks + i) * s.Rp + 32 * pr + 4 * q4;
+  auto store = [&](int bi) {
 #pragma unroll
-    for (int y = 0; y < 2; ++y) {
-      st4[2 * y] = *reinterpret_cast<const f32x4*>(p + 16 * y);
-      st4[2 * y + 1] = *reinterpret_cast<const f32x4*>(p + 16 * y + 2);
+    for (int t = 0; t < PW; ++t) {
+      char* dst = lds + bi * SB + (w + 4 * t) * 1024 + lane * 16;
+      *reinterpret_cast<u32x4*>(dst) = nq[t];
+      *reinterpret_cast<u32x4*>(dst + TB) = nd[t];
+    }
+    if (w == 0) *reinterpret_cast<float*>(lds + bi * SB + 2 * TB + lane * 4) = ns;
+  };
+  // S = Q K^T (kind 0) or dP = dO V^T (kind 1) of the unit, on top of the rows' statistics
+  auto scores = [&](int bi, int kind, const u32x4* bf) {
+    const char* b = lds + bi * SB;
+    const f32x4* st = reinterpret_cast<const f32x4*>(b + 2 * TB + kind * 128);
+    f32x16 c;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const f32x4 v = st[2 * x + h];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) c[4 * x + e] = v[e];
+    }
+#pragma unroll
+    for (int k = 0; k < NK; ++k) c = mfma32(ld16b(b + kind * TB + k * 1024 + fo[k & 1]), bf[k], c);
+    return c;
+  };
+  u32x4 pb[2], sb[2];  // P and dS of the current unit as operands
+  // one unit: P and dS of the next one (buffer b1), beside the current one's gradient products (b0)
+  auto unit = [&](auto B0, auto FIRST) {
+    constexpr int b0 = decltype(B0)::value, b1 = (b0 + 1) % 3, b2 = (b0 + 2) % 3;
+    lds_barrier();
+    store(b2);
+    fetch();
+    const int anchor = __builtin_amdgcn_readlane(myanc, wc.j);
+    next(wc);
+    const float bias = myk < anchor ? 0.f : -INFINITY;
+    const char* tq = lds + b0 * SB;
+    const char* td = tq + TB;
+    f32x16 sc = scores(b1, 0, kf);
+    f32x16 dp = scores(b1, 1, vf);
+    if constexpr (!decltype(FIRST)::value) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int dt = 0; dt < ND; ++dt) {
+          dv[dt] = mfma32(ld_tr_op(td, off, ks, dt), pb[ks], dv[dt]);
+          dk[dt] = mfma32(ld_tr_op(tq, off, ks, dt), sb[ks], dk[dt]);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) sc[e] = ex2(fmaf(sc[e], sl2, bias));
+#pragma unroll
+    for (int e = 0; e < 16; ++e) dp[e] *= sc[e];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      pb[ks] = pack_half(sc, ks);
+      sb[ks] = pack_half(dp, ks);
     }
   };
-
-  const char* L0 = reinterpret_cast<const char*>(&lds[0][0]);
-  int cj = take_block(), cp = 0;  // current unit: block i0 + cj, row pair cp
-  f32x4 cst[4], nst[4];
-  if (cj >= 0) {
-    stage(cj, cp, 0);
-    row_stats(cj, cp, cst);
+  if (units > 0) {
+    fetch();
+    store(0);
+    fetch();
+    unit(std::integral_constant<int, 2>{}, std::true_type{});  // stores unit 1, scores of unit 0
+    for (int u = 0; u < units; u += 3) {
+      unit(std::integral_constant<int, 0>{}, std::false_type{});
+      if (u + 1 < units) unit(std::integral_constant<int, 1>{}, std::false_type{});
+      if (u + 2 < units) unit(std::integral_constant<int, 2>{}, std::false_type{});
+    }
   }
-  wait_vm();
-  __syncthreads();
-  // one unit; the buffer index is a compile-time constant (units run in pairs), so every LDS
-  // read takes its buffer offset as an immediate
-  auto unit = [&](auto BI) {
-    constexpr int bi = decltype(BI)::value;
-    int nj = cj, np = cp + 1;
-    if (np == NPr) {
-      np = 0;
-      nj = take_block();
-    }
-    if (nj >= 0) {
-      stage(nj, np, bi ^ 1);
-      row_stats(nj, np, nst);
-    }
-    const int anchor = __builtin_amdgcn_readlane(anc, cj);
-    const bool vis = myk < anchor;  // this lane's key (column of every result tile)
-    const char* Lb = L0 + bi * NPc * 16;
-    // S = Q K^T, dP = dO V^T: A rows = pair rows 16 y + col
-    f32x4 sc[2], dp[2];
+  if (myk < s.T) {
+    float* pk = a.part + (((long)z * s.T + myk) * s.n_kv + g) * HD + 4 * h;
+    float* pv = a.part + ((((long)a.nch + z) * s.T + myk) * s.n_kv + g) * HD + 4 * h;
 #pragma unroll
-    for (int y = 0; y < 2; ++y) {
-      sc[y] = dp[y] = zero4();
-      const int rr = 16 * y + col;
+    for (int dt = 0; dt < ND; ++dt)
 #pragma unroll
-      for (int ks = 0; ks < HD / 32; ++ks) {
-        const int sl = rr * PK + ((ks * 4 + q4) ^ rsw<PK>(rr));
-        const u32x4 qa = *reinterpret_cast<const u32x4*>(Lb + sl * 16);
-        const u32x4 da = *reinterpret_cast<const u32x4*>(Lb + (RW * 64 + sl) * 16);
-        sc[y] = mfma(qa, kf[ks], sc[y]);
-        dp[y] = mfma(da, vf[ks], dp[y]);
+      for (int x = 0; x < 4; ++x) {
+        const f32x4 k4 = {dk[dt][4 * x], dk[dt][4 * x + 1], dk[dt][4 * x + 2], dk[dt][4 * x + 3]};
+        const f32x4 v4 = {dv[dt][4 * x], dv[dt][4 * x + 1], dv[dt][4 * x + 2], dv[dt][4 * x + 3]};
+        *reinterpret_cast<f32x4*>(pk + 32 * dt + 8 * x) = k4 * a.scale;
+        *reinterpret_cast<f32x4*>(pv + 32 * dt + 8 * x) = v4;
       }
-    }
-    f32x4 P[2], dS[2];
-#pragma unroll
-    for (int y = 0; y < 2; ++y)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const f32x4 sv = cst[2 * y + (e >> 1)];
-        const float l2 = sv[2 * (e & 1)], dr = sv[2 * (e & 1) + 1];
-        const float p = vis ? ex2(fmaf(sc[y][e], sl2, -l2)) : 0.f;
-        P[y][e] = p;
-        dS[y][e] = p * (dp[y][e] - dr);
-      }
-    const u32x4 pb = pack_bf8(P[0], P[1]), sb = pack_bf8(dS[0], dS[1]);
-#pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt) {
-      const int d = 16 * dt + col;
-      const int c0 = (q4 >> 1) ^ tsw(d), c1 = (2 + (q4 >> 1)) ^ tsw(d);
-      const int bq = 2 * RW * 64 + d * 4, bd = 3 * RW * 64 + d * 4;
-      const u32x2 q0 = *reinterpret_cast<const u32x2*>(Lb + (bq + c0) * 16 + (q4 & 1) * 8);
-      const u32x2 q1 = *reinterpret_cast<const u32x2*>(Lb + (bq + c1) * 16 + (q4 & 1) * 8);
-      const u32x2 o0 = *reinterpret_cast<const u32x2*>(Lb + (bd + c0) * 16 + (q4 & 1) * 8);
-      const u32x2 o1 = *reinterpret_cast<const u32x2*>(Lb + (bd + c1) * 16 + (q4 & 1) * 8);
-      dv[dt] = mfma(u32x4{o0[0], o0[1], o1[0], o1[1]}, pb, dv[dt]);
-      dk[dt] = mfma(u32x4{q0[0], q0[1], q1[0], q1[1]}, sb, dk[dt]);
-    }
-    wait_vm();
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < 4; ++e) cst[e] = nst[e];
-    cj = nj;
-    cp = np;
-  };
-  while (cj >= 0) {
-    unit(std::integral_constant<int, 0>{});
-    if (cj < 0) break;
-    unit(std::integral_constant<int, 1>{});
-  }
-  if (kok) {
-    float* pk = a.part + (((long)z * s.T + myk) * s.n_kv + g) * HD;
-    float* pv = a.part + ((((long)a.nch + z) * s.T + myk) * s.n_kv + g) * HD;
-#pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt) {
-      *reinterpret_cast<f32x4*>(pk + 16 * dt + 4 * q4) = dk[dt] * a.scale;
-      *reinterpret_cast<f32x4*>(pv + 16 * dt + 4 * q4) = dv[dt];
-    }
   }
 }
 
@@ -1017,8 +957,6 @@ static AttnShapeT att_shape(int n_blocks, int B, int T, int n_q, int n_kv, int h
   s.G = n_q / n_kv;
   s.R = s.G * B;
   s.Rp = (s.R + 31) / 32 * 32;
-  s.Tp = (T + 31) / 32 * 32 + 32;
-  s.Mp = n_blocks * 32;
   return s;
 }
 
@@ -1030,29 +968,28 @@ static int att_check(int n_blocks, int B, int T, int n_q, int n_kv, int hd) {
 }
 
 struct WsLayout {
-  size_t kct, vct, kbt, vbt, qt, dot, qr, dor, st, dob, dsum, part, order, total;
+  size_t st, qf, df, part, order, total;
   int nch;
 };
+
+// Chunks of the context-key gradients: at most 64 blocks each (one per lane of a wave), and enough
+// of them that the (key tile, KV head, chunk) work-groups fill 256 CUs twice, down to 4 blocks.
+static int kv_chunks(const AttnShapeT& s) {
+  const int least = (s.n_blocks + kChunkBlocks - 1) / kChunkBlocks, most = (s.n_blocks + 3) / 4;
+  const long per = (long)((s.T + kKvcKeys - 1) / kKvcKeys) * s.n_kv;
+  const int fill = per > 0 ? (int)((512 + per - 1) / per) : 1;
+  return std::max(least, std::min(fill, most));
+}
 
 static WsLayout ws_layout(const AttnShapeT& s) {
   WsLayout L{};
   auto al = [](size_t x) { return (x + 255) / 256 * 256; };
   size_t o = 0;
-  const size_t ctx_t = (size_t)s.n_kv * s.hd * s.Tp * 2, blk_t = (size_t)s.n_kv * s.hd * s.Mp * 2;
-  const size_t grp = (size_t)s.n_kv * s.n_blocks * s.hd * s.Rp * 2;
-  const size_t rows = (size_t)s.n_blocks * s.B * s.n_q;
-  L.nch = (s.n_blocks + kChunkBlocks - 1) / kChunkBlocks;
-  L.kct = o; o = al(o + ctx_t);
-  L.vct = o; o = al(o + ctx_t);
-  L.kbt = o; o = al(o + blk_t);
-  L.vbt = o; o = al(o + blk_t);
-  L.qt = o; o = al(o + grp);
-  L.dot = o; o = al(o + grp);
-  L.qr = o; o = al(o + grp);
-  L.dor = o; o = al(o + grp);
-  L.st = o; o = al(o + (size_t)s.n_kv * s.n_blocks * s.Rp * 8);
-  L.dob = o; o = al(o + rows * s.hd * 2);
-  L.dsum = o; o = al(o + rows * 4);
+  const size_t padded = (size_t)s.n_kv * s.n_blocks * s.Rp;
+  L.nch = kv_chunks(s);
+  L.st = o; o = al(o + padded * 8);
+  L.qf = o; o = al(o + padded * s.hd * 2);
+  L.df = o; o = al(o + padded * s.hd * 2);
   L.part = o; o = al(o + (size_t)2 * L.nch * s.T * s.n_kv * s.hd * 4);
   L.order = o; o = al(o + (size_t)s.n_blocks * 4);
   L.total = o;
@@ -1071,17 +1008,9 @@ static AttnT att_args(const AttnShapeT& s, const void* q, const void* kc, const 
   a.kb = (const uint16_t*)kb;
   a.vb = (const uint16_t*)vb;
   a.anchors = anchors;
-  a.kct = (uint16_t*)(w + L.kct);
-  a.vct = (uint16_t*)(w + L.vct);
-  a.kbt = (uint16_t*)(w + L.kbt);
-  a.vbt = (uint16_t*)(w + L.vbt);
-  a.qt = (uint16_t*)(w + L.qt);
-  a.dot = (uint16_t*)(w + L.dot);
-  a.dob = (uint16_t*)(w + L.dob);
-  a.qr = (uint16_t*)(w + L.qr);
-  a.dor = (uint16_t*)(w + L.dor);
-  a.st = (float2*)(w + L.st);
-  a.dsum = (float*)(w + L.dsum);
+  a.st = (float*)(w + L.st);
+  a.qf = (uint16_t*)(w + L.qf);
+  a.df = (uint16_t*)(w + L.df);
   a.part = (float*)(w + L.part);
   a.order = (int*)(w + L.order);
   a.nch = L.nch;
@@ -1089,14 +1018,40 @@ static AttnT att_args(const AttnShapeT& s, const void* q, const void* kc, const 
   return a;
 }
 
-static void transpose_kv(hipStream_t st, const uint16_t* src, int nrows, int cols, int ld, uint16_t* dst) {
-  hipLaunchKernelGGL(k_tr_kv_t, dim3((ld + 31) / 32, (cols + 31) / 32), dim3(256), 0, st, src, nrows, cols, ld, dst);
+static void launch_order(hipStream_t st, const AttnT& a) {
+  hipLaunchKernelGGL(k_anchor_order, dim3((a.s.n_blocks + 15) / 16), dim3(256), 0, st, a.anchors, a.s.n_blocks, a.s.T,
+                     a.order);
+}
+
+template <int HD, bool DQ, int WPB, int KS>
+static void launch_rows_as(hipStream_t st, const AttnT& a) {
+  constexpr int NB = KS > 1 ? 1 : 4 / WPB;
+  const int units = ((a.s.n_blocks + NB - 1) / NB + 7) / 8 * 8;  // whole turns of the 8 XCDs
+  hipLaunchKernelGGL((k_aatt_rows<HD, DQ, WPB, KS>), dim3(units * a.s.n_kv), dim3(kTrT), 0, st, a);
 }
 
 template <typename F>
 static void by_hd(int hd, F&& f) {
   if (hd == 64) f(std::integral_constant<int, 64>{});
   else f(std::integral_constant<int, 128>{});
+}
+
+// The row kernel's form.  A wave takes 32 of a block's R rows, so a block is WPB = ceil(R / 32)
+// waves; the work-group's other waves take further blocks where there are enough of them to
+// occupy the chip (kRowsSplitMax), else the same block's other key tiles.
+template <bool DQ>
+static void launch_rows(hipStream_t st, const AttnT& a) {
+  const AttnShapeT& s = a.s;
+  const bool split = (long)s.n_blocks * s.n_kv <= kRowsSplitMax;
+  by_hd(s.hd, [&](auto h) {
+    constexpr int HD = decltype(h)::value;
+    switch (s.Rp / 32) {
+      case 1: return split ? launch_rows_as<HD, DQ, 1, 4>(st, a) : launch_rows_as<HD, DQ, 1, 1>(st, a);
+      case 2: return split ? launch_rows_as<HD, DQ, 2, 2>(st, a) : launch_rows_as<HD, DQ, 2, 1>(st, a);
+      case 3: return launch_rows_as<HD, DQ, 3, 1>(st, a);
+      default: return launch_rows_as<HD, DQ, 4, 1>(st, a);
+    }
+  });
 }
 
 }  // namespace dflare
@@ -1125,17 +1080,8 @@ int dflare_anchor_attention_fwd(const void* q, const void* k_ctx, const void* v_
   AttnT a = att_args(s, q, k_ctx, v_ctx, k_blk, v_blk, anchors, workspace);
   a.out = out;
   a.lse = lse;
-  const int cols = n_kv * hd;
-  const uint16_t* zero_src = a.kb;  // with T = 0 the context copies are all zeros
-  transpose_kv(st, T > 0 ? a.vc : zero_src, T, cols, s.Tp, a.vct);
-  hipLaunchKernelGGL(k_tr_blk_t, dim3(n_blocks, (cols + 255) / 256), dim3(256), 0, st, a.vb, n_blocks, B, cols, a.vbt);
-  hipLaunchKernelGGL(k_anchor_order, dim3((n_blocks + 63) / 64), dim3(256), 0, st, anchors, n_blocks, T, a.order);
-  const bool two = (s.R + 15) / 16 > 4;
-  by_hd(hd, [&](auto h) {
-    constexpr int HD = decltype(h)::value;
-    if (two) hipLaunchKernelGGL((k_aatt_rows<HD, false, 2>), dim3(n_blocks, n_kv), dim3(kTrT), 0, st, a);
-    else hipLaunchKernelGGL((k_aatt_rows<HD, false, 1>), dim3(n_blocks, n_kv), dim3(kTrT), 0, st, a);
-  });
+  launch_order(st, a);
+  launch_rows<false>(st, a);
   return hipGetLastError() == hipSuccess ? DFLARE_OK : DFLARE_ERR_HIP;
 }
 
@@ -1161,20 +1107,17 @@ int dflare_anchor_attention_bwd(const void* q, const void* k_ctx, const void* v_
   a.dvc = dv_ctx;
   a.dkb = dk_blk;
   a.dvb = dv_blk;
-  const int cols = n_kv * hd;
-  const uint16_t* zero_src = a.kb;
-  transpose_kv(st, T > 0 ? a.kc : zero_src, T, cols, s.Tp, a.kct);
-  hipLaunchKernelGGL(k_tr_blk_t, dim3(n_blocks, (cols + 255) / 256), dim3(256), 0, st, a.kb, n_blocks, B, cols, a.kbt);
-  hipLaunchKernelGGL(k_anchor_order, dim3((n_blocks + 63) / 64), dim3(256), 0, st, anchors, n_blocks, T, a.order);
+  launch_order(st, a);
   by_hd(hd, [&](auto h) {
     constexpr int HD = decltype(h)::value;
-    hipLaunchKernelGGL((k_bwd_prep<HD>), dim3(n_blocks, n_kv), dim3(256), (size_t)4 * HD * s.Rp, st, a.q, dout, out,
-                       (const float*)a.lse, s, a.dob, a.dsum, a.qr, a.dor, a.st, a.qt, a.dot);
-    if ((s.R + 15) / 16 > 4) hipLaunchKernelGGL((k_aatt_rows<HD, true, 2>), dim3(n_blocks, n_kv), dim3(kTrT), 0, st, a);
-    else hipLaunchKernelGGL((k_aatt_rows<HD, true, 1>), dim3(n_blocks, n_kv), dim3(kTrT), 0, st, a);
-    hipLaunchKernelGGL((k_aatt_kvb<HD>), dim3(n_blocks, n_kv, 1), dim3(kTrT), 0, st, a);
-    if (T > 0) hipLaunchKernelGGL((k_aatt_kvc<HD>), dim3((T + 63) / 64, n_kv, a.nch), dim3(kTrT), 0, st, a);
+    hipLaunchKernelGGL((k_bwd_prep<HD>), dim3((n_blocks + 7) / 8 * 8 * n_kv), dim3(kTrT), (size_t)(4 * HD + 8) * s.Rp, st, a, out);
   });
+  launch_rows<true>(st, a);
+  if (T > 0)
+    by_hd(hd, [&](auto h) {
+      constexpr int HD = decltype(h)::value;
+      hipLaunchKernelGGL((k_aatt_kvc<HD>), dim3((T + kKvcKeys - 1) / kKvcKeys, n_kv, a.nch), dim3(kTrT), 0, st, a);
+    });
   if (T > 0) {
     const long n = (long)T * n_kv * hd;
     hipLaunchKernelGGL(k_aatt_sum, dim3((int)std::min<long>((n + 255) / 256, 4096)), dim3(256), 0, st, a.part, a.nch,

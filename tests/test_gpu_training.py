@@ -78,6 +78,33 @@ def test_anchor_attention_matches_oracle(name):
           + " ".join(f"{k} {v:.2e}" for k, v in errs.items()), flush=True)
 
 
+# Edges of the attention kernels' forms: rows per (block, KV head) of one to four 32-row waves, with
+# and without padding; blocks few enough for split key tiles and more (257 blocks x 1 head: a last
+# work-group that is not full); contexts at the edges of the 32-key and 128-key tiles; anchors
+# at tile edges.  The bar is that of the cases above.
+@pytest.mark.parametrize("n,B,T,nq,nkv,hd", [
+    (3, 16, 1, 2, 1, 128), (257, 16, 33, 2, 1, 64), (258, 3, 31, 3, 1, 128),      # one wave per block
+    (5, 16, 129, 4, 1, 64), (261, 11, 65, 4, 1, 128), (129, 16, 127, 8, 2, 64),   # two
+    (9, 11, 128, 8, 1, 64), (33, 16, 160, 6, 1, 128),                             # three
+    (7, 16, 257, 8, 1, 128), (70, 13, 96, 16, 2, 64),                             # four
+])
+def test_anchor_attention_kernel_forms(n, B, T, nq, nkv, hd):
+    print(f"[training] attention form {(n, B, T, nq, nkv, hd)}", flush=True)
+    x, anchors, dout = inputs(n, B, T, nq, nkv, hd, seed=5)
+    edges = [a for a in (0, 1, 31, 32, 33, 127, 128, 129, T - 1, T) if 0 <= a <= T][:n]
+    anchors[:len(edges)] = edges
+    f64 = {k: synth.bf16_to_f32(v).astype(np.float64) for k, v in x.items()}
+    d = {k: dev(v) for k, v in x.items()}
+    a = torch.from_numpy(anchors).cuda()
+    inp = (d["q"], d["k_ctx"], d["v_ctx"], d["k_blk"], d["v_blk"], a, B)
+    out, lse = dfl.anchor_attention_fwd(*inp)
+    got = (out, lse, *dfl.anchor_attention_bwd(*inp, out, lse, torch.from_numpy(dout.astype(np.float32)).cuda()))
+    want = (*tr.anchor_attention_fwd(**f64, anchors=list(anchors), B=B),
+            *tr.anchor_attention_bwd(**f64, anchors=list(anchors), B=B, dout=dout))
+    for nm, u, v in zip(("out", "lse", "dq", "dk_ctx", "dv_ctx", "dk_blk", "dv_blk"), got, want):
+        assert P.relinf(u.cpu().numpy(), v) <= P.REL_TOL, (nm, P.relinf(u.cpu().numpy(), v))
+
+
 # (V, blocks): rows streamed twice (V = 1000, 1003), and rows held on chip (V a multiple of 4 in
 # 111,616 .. 152,512): none in LDS, the Qwen3 vocabulary, LDS full; 17 blocks = 272 rows give
 # work-groups a second row
