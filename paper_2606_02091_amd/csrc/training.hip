@@ -723,6 +723,8 @@ __global__ void k_aatt_sum(const float* part, int nch, long n, float* dk, float*
 // flight at a time); last, the loss in row order. ----
 constexpr int kCeT = 1024;       // threads of the row work-group
 constexpr int kCeRows = 256;     // rows in flight (work-groups)
+constexpr int kCePieces = 512;   // work-groups of a last turn of rows cut into pieces
+constexpr int kCeTailMax = 64;   // rows of such a turn: from there both ways cost the same (151,936 values, 90 us)
 
 // w[r] = exp(-(b - 1) / gamma) for block position b = r mod B > 0 with a label in range, else 0;
 // 1 / sum w in fp64, summed in the loss kernel's order
@@ -745,78 +747,118 @@ __global__ __launch_bounds__(256) void k_wce_weights(const int32_t* labels, int 
   if (threadIdx.x == 0) inv_wsum[0] = sw[0] > 0.0 ? (float)(1.0 / sw[0]) : 0.f;
 }
 
-// per row: lse (log2 domain: max of z log2 e, sum of 2^(z log2 e - max)), ce = lse - z[label]
-// for rows that take part, and dz = (w / sum w) (softmax(z) - onehot(label)), four values per
-// thread per step where the row allows 16-byte accesses (V % 4 == 0)
-__global__ __launch_bounds__(kCeT) void k_wce_fused(const float* logits, const int32_t* labels, int rows, int V,
-                                                    int B, const float* w, const float* inv_wsum, float* ce_out,
-                                                    float* dz) {
-  __shared__ float sm[kCeT / 64], ss[kCeT / 64];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const float L2E = 1.4426950408889634f;
-  const int V4 = (V % 4 == 0) ? V / 4 : 0;
-  const float inv = inv_wsum[0];
-  for (int row = blockIdx.x; row < rows; row += gridDim.x) {
-    const float* z = logits + (long)row * V;
-    float m = -INFINITY, sum = 0.f;
-    for (int v = threadIdx.x; v < V4; v += kCeT) {
-      const f32x4 x = reinterpret_cast<const f32x4*>(z)[v];
-      const float t0 = x[0] * L2E, t1 = x[1] * L2E, t2 = x[2] * L2E, t3 = x[3] * L2E;
-      const float m4 = fmaxf(fmaxf(t0, t1), fmaxf(t2, t3));
-      if (m4 > m) {
-        sum *= ex2(m - m4);
-        m = m4;
-      }
-      sum += (ex2(t0 - m) + ex2(t1 - m)) + (ex2(t2 - m) + ex2(t3 - m));
-    }
-    for (int v = 4 * V4 + threadIdx.x; v < V; v += kCeT) {
-      const float t = z[v] * L2E;
-      if (t > m) {
-        sum *= ex2(m - t);
-        m = t;
-      }
-      sum += ex2(t - m);
-    }
+// max or sum over a work-group of T threads, the same value in every thread (fixed order)
+template <int T, bool MAX>
+__device__ __forceinline__ float ce_reduce(float v, float* red) {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const float om = __shfl_xor(m, off), os = __shfl_xor(sum, off);
-      const float nm = fmaxf(m, om);
-      sum = (nm == -INFINITY) ? 0.f : sum * ex2(m - nm) + os * ex2(om - nm);
-      m = nm;
-    }
-    if (lane == 0) {
-      sm[wv] = m;
-      ss[wv] = sum;
-    }
-    __syncthreads();
-    float M = sm[0], S = ss[0];
-#pragma unroll
-    for (int k = 1; k < kCeT / 64; ++k) {
-      const float nm = fmaxf(M, sm[k]);
-      S = S * ex2(M - nm) + ss[k] * ex2(sm[k] - nm);
-      M = nm;
-    }
-    __syncthreads();  // sm, ss are rewritten by the next row
-    const float lse2 = M + log2f(S);
-    const int y = labels[row];
-    const bool on = row % B > 0 && y >= 0 && y < V;
-    if (threadIdx.x == 0) ce_out[row] = on ? lse2 * 0.6931471805599453f - z[y] : 0.f;
-    const float c = w[row] * inv;
-    float* d = dz + (long)row * V;
-    const int y4 = (on && c != 0.f) ? y >> 2 : -1;
-    for (int v = threadIdx.x; v < V4; v += kCeT) {
-      f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (c != 0.f) {
-        const f32x4 x = reinterpret_cast<const f32x4*>(z)[v];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = c * ex2(fmaf(x[e], L2E, -lse2));
-        if (v == y4) o[y & 3] -= c;
-      }
-      __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(d) + v);
-    }
-    for (int v = 4 * V4 + threadIdx.x; v < V; v += kCeT)
-      d[v] = c == 0.f ? 0.f : c * ex2(fmaf(z[v], L2E, -lse2)) - (on && v == y ? c : 0.f);
+  for (int off = 32; off > 0; off >>= 1) {
+    const float o = __shfl_xor(v, off);
+    v = MAX ? fmaxf(v, o) : v + o;
   }
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  v = red[0];
+#pragma unroll
+  for (int k = 1; k < T / 64; ++k) v = MAX ? fmaxf(v, red[k]) : v + red[k];
+  return v;
+}
+
+// per row: lse (log2 domain: max of z log2 e, sum of 2^(z log2 e - max)), ce = lse - z[label] for
+// rows that take part, and dz = (w / sum w) (softmax(z) - onehot(label)).  One work-group per row, which
+// holds S 16-byte pieces per thread in registers, all their loads in flight together, so that
+// rows of up to 4 S T values are read once; of longer rows (REST) the values past those are read again
+// for the gradient.  The pieces start at the row's first aligned value; the up to 6 values before and
+// after them go to the first threads.  Rows without a loss get zeros and are not read.
+// Bound by memory and, with few rows, by the latency of one row.  Against two sweeps per row by
+// 1,024 threads, with single-value accesses where 4 does not divide V (whole call): 207 rows x 32,003
+// 31 -> 19 us, 4,800 x 4,000 74 -> 37, 1,600 x 98,000 317 -> 246, 528 x 100,001 284 -> 96, 1,040 x 201,088
+// (with the last turn in pieces, below) 441 -> 357.
+template <int T, int S, bool REST>
+__global__ __launch_bounds__(T) void k_wce_reg(const float* logits, const int32_t* labels, int V, int B,
+                                               const float* w, const float* inv_wsum, float* ce_out, float* dz) {
+  __shared__ float red[T / 64];
+  const int row = blockIdx.x, tid = threadIdx.x;
+  const float L2E = 1.4426950408889634f;
+  const float* z = logits + (long)row * V;
+  float* d = dz + (long)row * V;
+  const int y = labels[row];
+  const bool on = row % B > 0 && y >= 0 && y < V;
+  const int head = min(V, (int)((0u - (unsigned)(reinterpret_cast<uintptr_t>(z) >> 2)) & 3u));
+  const int n4 = (V - head) / 4, tail = V - head - 4 * n4;
+  const int edge = tid < head ? tid : tid < head + tail ? V - tail + tid - head : -1;
+  const f32x4* z4 = reinterpret_cast<const f32x4*>(z + head);
+  const f32x4 none = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  f32x4 r[S];
+  float e1 = -INFINITY;
+  float lse2 = 0.f;
+  auto max4 = [](f32x4 x) { return fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])); };
+  auto exp4 = [&](f32x4 x, float m) {
+    return (ex2(fmaf(x[0], L2E, -m)) + ex2(fmaf(x[1], L2E, -m))) + (ex2(fmaf(x[2], L2E, -m)) + ex2(fmaf(x[3], L2E, -m)));
+  };
+  if (on) {
+    if (n4 > 0) {
+#pragma unroll
+      for (int k = 0; k < S; ++k) r[k] = z4[min(k * T + tid, n4 - 1)];
+    }
+    if (edge >= 0) e1 = z[edge];
+    float m = e1;
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+      if (k * T + tid >= n4) r[k] = none;
+      m = fmaxf(m, max4(r[k]));
+    }
+    float rest = 0.f;
+    if constexpr (REST) {  // running (max, sum) of the values past the registers, four pieces at a time
+      for (int v = S * T + tid; v < n4; v += 4 * T) {
+        f32x4 x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = z4[min(v + k * T, n4 - 1)];
+#pragma unroll
+        for (int k = 1; k < 4; ++k)
+          if (v + k * T >= n4) x[k] = none;
+        const float mx = fmaxf(fmaxf(max4(x[0]), max4(x[1])), fmaxf(max4(x[2]), max4(x[3])));
+        if (mx > m) {
+          rest *= ex2((m - mx) * L2E);
+          m = mx;
+        }
+        const float ml = m * L2E;
+        rest += (exp4(x[0], ml) + exp4(x[1], ml)) + (exp4(x[2], ml) + exp4(x[3], ml));
+      }
+    }
+    const float M = ce_reduce<T, true>(m, red) * L2E;
+    float sum = ex2(fmaf(e1, L2E, -M));
+#pragma unroll
+    for (int k = 0; k < S; ++k) sum += exp4(r[k], M);
+    if (REST && S * T + tid < n4) sum += rest * ex2(fmaf(m, L2E, -M));
+    lse2 = M + log2f(ce_reduce<T, false>(sum, red));
+  }
+  if (tid == 0) ce_out[row] = on ? lse2 * 0.6931471805599453f - z[y] : 0.f;
+  const float c = on ? w[row] * inv_wsum[0] : 0.f;
+  const int yv = c != 0.f ? y - head : -1;  // the label's place after the first aligned value
+  const bool wide = (reinterpret_cast<uintptr_t>(d + head) & 15) == 0;  // (the gradient may be aligned otherwise)
+  auto grad = [&](f32x4 x, int v) {
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    if (c != 0.f) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        o[e] = c * ex2(fmaf(x[e], L2E, -lse2));
+        if (4 * v + e == yv) o[e] -= c;
+      }
+    }
+    if (wide) __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(d + head) + v);
+    else
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d[head + 4 * v + e] = o[e];
+  };
+  if constexpr (REST) {  // first: its values were read last
+#pragma unroll 4
+    for (int v = S * T + tid; v < n4; v += T) grad(c != 0.f ? z4[v] : none, v);
+  }
+#pragma unroll
+  for (int k = 0; k < S; ++k)
+    if (k * T + tid < n4) grad(r[k], k * T + tid);
+  if (edge >= 0) d[edge] = c == 0.f ? 0.f : c * ex2(fmaf(e1, L2E, -lse2)) - (edge == y ? c : 0.f);
 }
 
 // The same per row with the whole row held on chip: one work-group per CU (its LDS share is
@@ -916,6 +958,67 @@ __global__ __launch_bounds__(kCeOT) void k_wce_chip(const float* logits, const i
       }
     }
     __syncthreads();  // lrow is refilled by the next row
+  }
+}
+
+// The rows of a last, nearly empty turn of the kernel above, each cut into `pieces` for as many
+// work-groups: pass 0 leaves each piece's (max, sum of 2^(z log2 e - max)) in part, pass 1 forms the row's
+// from them in piece order and writes the gradient.  As above, rows without a weight give exact
+// zeros where `zero_off`.
+template <int PASS>
+__global__ __launch_bounds__(kCeT) void k_wce_piece(const float* logits, const int32_t* labels, int row0, int pieces,
+                                                    int V, int B, const float* w, const float* inv_wsum, float* part,
+                                                    float* ce_out, float* dz, bool zero_off) {
+  __shared__ float red[kCeT / 64];
+  const int row = row0 + blockIdx.x / pieces, pc = blockIdx.x % pieces, tid = threadIdx.x;
+  const float L2E = 1.4426950408889634f;
+  const int V4 = V / 4, v0 = (int)((long)V4 * pc / pieces), v1 = (int)((long)V4 * (pc + 1) / pieces);
+  const f32x4* z4 = reinterpret_cast<const f32x4*>(logits + (long)row * V);
+  if constexpr (PASS == 0) {
+    float m = -INFINITY;
+#pragma unroll 4
+    for (int v = v0 + tid; v < v1; v += kCeT) {
+      const f32x4 x = z4[v];
+      m = fmaxf(m, fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
+    }
+    const float M = ce_reduce<kCeT, true>(m, red) * L2E;
+    float sum = 0.f;
+#pragma unroll 4
+    for (int v = v0 + tid; v < v1; v += kCeT) {
+      const f32x4 x = z4[v];
+      sum += (ex2(fmaf(x[0], L2E, -M)) + ex2(fmaf(x[1], L2E, -M))) +
+             (ex2(fmaf(x[2], L2E, -M)) + ex2(fmaf(x[3], L2E, -M)));
+    }
+    sum = ce_reduce<kCeT, false>(sum, red);
+    if (tid == 0) {
+      part[2 * blockIdx.x] = M;
+      part[2 * blockIdx.x + 1] = sum;
+    }
+  } else {
+    const float* pp = part + 2 * (blockIdx.x - pc);
+    float M = pp[0], S = pp[1];
+    for (int k = 1; k < pieces; ++k) {
+      const float nm = fmaxf(M, pp[2 * k]);
+      if (nm != -INFINITY) S = S * ex2(M - nm) + pp[2 * k + 1] * ex2(pp[2 * k] - nm);
+      M = nm;
+    }
+    const float lse2 = M + log2f(S);
+    const int y = labels[row];
+    const bool on = row % B > 0 && y >= 0 && y < V;
+    if (tid == 0 && pc == 0) ce_out[row] = on ? lse2 * 0.6931471805599453f - logits[(long)row * V + y] : 0.f;
+    const float c = w[row] * inv_wsum[0];
+    f32x4* d4 = reinterpret_cast<f32x4*>(dz + (long)row * V);
+#pragma unroll 4
+    for (int v = v0 + tid; v < v1; v += kCeT) {
+      f32x4 o = zero4();
+      if (!(zero_off && c == 0.f)) {
+        const f32x4 x = z4[v];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = c * ex2(fmaf(x[e], L2E, -lse2));
+        if (on && v == y >> 2) o[y & 3] -= c;
+      }
+      __builtin_nontemporal_store(o, d4 + v);
+    }
   }
 }
 
@@ -1126,25 +1229,51 @@ int dflare_anchor_attention_bwd(const void* q, const void* k_ctx, const void* v_
   return hipGetLastError() == hipSuccess ? DFLARE_OK : DFLARE_ERR_HIP;
 }
 
-size_t dflare_weighted_ce_workspace(int32_t rows) { return ((size_t)3 * rows + 64) * 4; }
+size_t dflare_weighted_ce_workspace(int32_t rows) { return ((size_t)3 * rows + 64 + 2 * kCePieces) * 4; }
 
 }  // extern "C"
 
 namespace {
 
-// The four launches of the weighted CE; w holds at least rows + 1 floats (the row weights,
-// then 1 / sum w), every one written by the first launch before any other reads it.
+// The launches of the weighted CE; w holds at least rows + 64 + 2 kCePieces floats (the row weights,
+// 1 / sum w, from rows + 64 on the partial sums of pieces), every one written by an earlier launch
+// of the call than reads it.
 void launch_weighted_ce(hipStream_t st, const float* logits, const int32_t* labels, int32_t rows, int32_t V,
                         int32_t B, float gamma, float* loss, float* row_ce, float* dlogits, float* w) {
-  float* inv = w + rows;
-  hipLaunchKernelGGL(k_wce_weights, dim3(1), dim3(256), 0, st, labels, rows, V, B, gamma, w, inv);
-  if (V % 4 == 0 && (long)V >= kCeOMin && (long)V <= kCeOCap)
-    hipLaunchKernelGGL(k_wce_chip, dim3(std::min(rows, kCeRows)), dim3(kCeOT), 0, st, logits, labels, rows, V, B,
-                       (const float*)w, (const float*)inv, row_ce, dlogits);
-  else
-    hipLaunchKernelGGL(k_wce_fused, dim3(std::min(rows, kCeRows)), dim3(kCeT), 0, st, logits, labels, rows, V, B,
-                       (const float*)w, (const float*)inv, row_ce, dlogits);
-  hipLaunchKernelGGL(k_wce_loss, dim3(1), dim3(256), 0, st, w, row_ce, rows, loss);
+  const float *wr = w, *inv = w + rows;
+  float* part = w + rows + 64;
+  hipLaunchKernelGGL(k_wce_weights, dim3(1), dim3(256), 0, st, labels, rows, V, B, gamma, w, w + rows);
+  auto reg = [&](auto kernel, int n, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(n), dim3(threads), 0, st, logits, labels, V, B, wr, inv, row_ce, dlogits);
+  };
+  // rows that fit the registers of a work-group: the fewest threads that hold them, so that several
+  // rows share a CU (300 x 16 rows of 4,000 values: 4 waves 37 us, 16 waves 74)
+  const int n4 = V / 4;
+  if (n4 <= 512) reg(k_wce_reg<256, 2, false>, rows, 256);
+  else if (n4 <= 2048) reg(k_wce_reg<256, 8, false>, rows, 256);
+  else if (n4 <= 4096) reg(k_wce_reg<256, 16, false>, rows, 256);
+  else if (n4 <= 8192) reg(k_wce_reg<512, 16, false>, rows, 512);
+  else if (n4 <= 12288) reg(k_wce_reg<512, 24, false>, rows, 512);
+  else if (n4 <= 16384) reg(k_wce_reg<1024, 16, false>, rows, 1024);
+  else if (n4 <= 24576) reg(k_wce_reg<1024, 24, false>, rows, 1024);
+  else {
+    // longer ones turn by turn of a row per CU, a nearly empty last turn cut into pieces
+    const int last = rows % kCeRows, tail = V % 4 == 0 && last <= kCeTailMax ? last : 0, full = rows - tail;
+    const bool chip = V % 4 == 0 && (long)V >= kCeOMin && (long)V <= kCeOCap;
+    if (full > 0 && chip)
+      hipLaunchKernelGGL(k_wce_chip, dim3(std::min(full, kCeRows)), dim3(kCeOT), 0, st, logits, labels, full, V, B, wr,
+                         inv, row_ce, dlogits);
+    else if (full > 0)
+      reg(k_wce_reg<1024, 20, true>, full, 1024);
+    if (tail > 0) {
+      const int pieces = kCePieces / tail;
+      hipLaunchKernelGGL((k_wce_piece<0>), dim3(tail * pieces), dim3(kCeT), 0, st, logits, labels, full, pieces, V, B,
+                         wr, inv, part, row_ce, dlogits, !chip);
+      hipLaunchKernelGGL((k_wce_piece<1>), dim3(tail * pieces), dim3(kCeT), 0, st, logits, labels, full, pieces, V, B,
+                         wr, inv, part, row_ce, dlogits, !chip);
+    }
+  }
+  hipLaunchKernelGGL(k_wce_loss, dim3(1), dim3(256), 0, st, wr, row_ce, rows, loss);
 }
 
 bool ce_args_ok(const float* logits, const int32_t* labels, int32_t rows, int32_t V, int32_t B, float gamma,
@@ -1158,7 +1287,7 @@ bool ce_args_ok(const float* logits, const int32_t* labels, int32_t rows, int32_
 // array's name is not a device address: kernels get the address hipGetSymbolAddress returns
 // for the current device, looked up once per device.
 constexpr int kCeNoAllocMaxRows = DFLARE_WEIGHTED_CE_NOALLOC_MAX_ROWS;
-__device__ __align__(256) float scratch[kCeNoAllocMaxRows + 64];
+__device__ __align__(256) float scratch[kCeNoAllocMaxRows + 64 + 2 * kCePieces];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;

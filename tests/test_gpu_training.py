@@ -105,10 +105,13 @@ def test_anchor_attention_kernel_forms(n, B, T, nq, nkv, hd):
         assert P.relinf(u.cpu().numpy(), v) <= P.REL_TOL, (nm, P.relinf(u.cpu().numpy(), v))
 
 
-# (V, blocks): rows streamed twice (V = 1000, 1003), and rows held on chip (V a multiple of 4 in
-# 111,616 .. 152,512): none in LDS, the Qwen3 vocabulary, LDS full; 17 blocks = 272 rows give
-# work-groups a second row
-@pytest.mark.parametrize("V,n", [(1000, 6), (1003, 6), (111616, 17), (151936, 2), (152512, 2)])
+# (V, blocks): rows held in registers (up to 98,307 values: odd row starts, the last value of each
+# size), rows with a part past the registers (98,309; 152,516 and 201,088), and rows held on chip (V a
+# multiple of 4 in 111,616 .. 152,512): none in LDS, the Qwen3 vocabulary, LDS full; 17 blocks = 272
+# rows: a last turn of 16 rows cut into pieces, 23 = 368: one of 112 rows that is not
+@pytest.mark.parametrize("V,n", [(3, 2), (1000, 6), (1003, 6), (1000, 70), (2051, 3), (8195, 3), (16387, 3), (32003, 9),
+                                 (49155, 2), (65539, 2), (98307, 2), (98309, 2), (111616, 17), (111616, 23), (151936, 2),
+                                 (152512, 2), (152516, 17), (201088, 2)])
 def test_weighted_ce_matches_oracle(V, n):
     B = 16
     rng = np.random.default_rng(3)
