@@ -36,7 +36,8 @@ struct BRows {
 // (the MFMA A-operand layout of the activations, one plane); W: packed weight tiles in
 // fp16 [layers][Nt][Kt][64].  Work-group = (layer, K part,
 // 256-column n-group, 128-row m-group); with kg > 1 the K parts of a tile leave fp32
-// partial tiles and the last to arrive sums them in K order and runs the epilogue.
+// partial tiles and the last to arrive sums them in K order and runs the epilogue (RESID: plain rows
+// [kg][Mt * 16][H], which k_bnorm adds to the residual stream).
 struct BGemmArgs {
   const u32x4* A;
   long a_layer;   // u32x4 units between layers

@@ -193,7 +193,26 @@ __global__ __launch_bounds__(kBT) __attribute__((amdgpu_waves_per_eu(kBWavesPerS
     }
   }
 
-  if (g.kg > 1) {
+  if constexpr (EPI == BEPI_RESID) {
+    if (g.kg > 1) {
+      // split K: this part's sums stay in part [kg][Mt * 16][H] for the norm that follows, which adds
+      // them to X (512 rows, H = 4,096, F = 12,288, 4 parts: against the exchange below output 45 -> 28 us,
+      // down 78 -> 61, the norm 7 -> 12)
+#pragma unroll
+      for (int n = 0; n < NW; ++n) {
+        const int nt = nt0 + n;
+        if (nt >= g.Nt) continue;
+        float* dst = g.part + ((long)kz * g.Mt * 16 + mg * kBM * 16 + quad * 4) * g.H + nt * 16 + col;
+#pragma unroll
+        for (int m = 0; m < kBM; ++m) {
+          if (mg * kBM + m >= g.Mt) continue;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dst[(long)(m * 16 + e) * g.H] = acc[m][n][e];
+        }
+      }
+      return;
+    }
+  } else if (g.kg > 1) {
     // split K: leave this part's tile, then the last part to arrive sums all parts in K order
     // (each 1 KiB block: elements 0-1 of the 64 lanes, then elements 2-3, so that every
     // 8-byte store or load instruction covers 512 contiguous bytes)

@@ -991,7 +991,7 @@ int bgemm(dflare_handle* h, int kind, const char* name, int epi, BGemmArgs& g, c
     launch_bgemm(h->stream, epi, g, rows);
   }
   prof_mark(h, kind, false);
-  return ss.tn && epi == BEPI_RESID ? ss.kg : 0;
+  return epi == BEPI_RESID && (ss.tn || g.kg > 1) ? g.kg : 0;
 }
 
 // epilogue fields shared by every batched GEMM of a handle

@@ -176,6 +176,21 @@ def test_batched_few_rows(hidden, n_q, n_kv, hd, ffn):
     model.close()
 
 
+# calls of nine and ten row tiles on the tiled GEMM, whose residual projections leave their K parts to
+# the norm: a second group of row tiles that is not full, a last column group that is not (66
+# output tiles), parts of unequal length (33 and 65 k-tiles), ragged rows (B = 13)
+def test_batched_residual_parts():
+    cfg = synth.ModelConfig("parts", hidden=1056, n_q_heads=8, n_kv_heads=2, head_dim=128, ffn=2080, vocab=501,
+                            n_draft_layers=2, n_target_layers=3, block_size=13, context=40, random_block=True)
+    slots = [5, 0, 3, 9, 1, 7, 2, 8, 4, 11, 6, 10]
+    print("[batched] residual parts", flush=True)
+    model, orcs, _ = build_batched(cfg, [40, 7, 0, 16, 33, 1, 12, 25, 18, 3, 39, 22], slots, 12)
+    for n in (11, 12):
+        _, _, worst = compare_draft(model, orcs, cfg, slots[:n])
+        print(f"[batched] residual parts: {n} sequences, logits rel err {worst:.2e}", flush=True)
+    model.close()
+
+
 def test_batched_single_equals_batch1():
     """Slot 0 through the batch-1 calls, slot 1 through the batched calls, same rows."""
     cfg = CASES["hd128_b16"][0]
