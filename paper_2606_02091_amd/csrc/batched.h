@@ -14,7 +14,8 @@ constexpr int kBM = 8;                   // m-tiles per work-group (128 rows); e
 constexpr int kBNW = 4;                  // n-tiles per wave (64 columns); 3 for some shapes (BGemmArgs::nw)
 constexpr int kBN = kBWaves * kBNW;      // n-tiles per work-group (256 columns)
 constexpr int kMaxSeq = 64;              // sequences in one batched call
-constexpr int kBKeys = 512;              // keys (context and block) per batched attention work item
+constexpr int kBKeys = 512;              // most keys (context and block) per batched attention work item
+constexpr int kBKeysMin = 128;           // fewest (calls of few work items)
 constexpr int kBSplitMax = 8;            // K parts of one batched GEMM output tile
 constexpr long kBPartFloats = (long)kBWaves * kBM * kBNW * 256;  // one work-group's partial tile
 constexpr int kBCounters = 4096;         // split-K arrival counters (output tiles of one launch)
@@ -23,13 +24,14 @@ enum BEpi { BEPI_QKV = 0, BEPI_RESID = 1, BEPI_SWIGLU = 2, BEPI_ARGMAX = 3, BEPI
 
 // Rows of one batched call, passed by value: call sequence i (cache slot seq[i], context
 // length L[i]) owns rows off[i] .. off[i+1]-1 of the call's activations; its attention work
-// items are ipfx[i] .. ipfx[i+1]-1 (n_kv per range of kBKeys keys of its L + B keys).
+// items are ipfx[i] .. ipfx[i+1]-1 (n_kv per range of `keys` keys of its L + B keys).
 struct BRows {
   int n_seq;
   int seq[kMaxSeq];
   int L[kMaxSeq];
   int off[kMaxSeq + 1];
   int ipfx[kMaxSeq + 1];
+  int keys;
 };
 
 // Y = A W^T with a fused epilogue.  A: fp16 A fragments [layers][Mt][Kt][64 lanes x 16 B]

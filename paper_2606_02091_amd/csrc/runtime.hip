@@ -148,6 +148,7 @@ struct dflare_handle {
   long seq_stride = 0;     // cache elements of one sequence slot (all layers)
   int b_mt = 1;            // m-tiles of the largest batched call
   float *bX = nullptr, *bQ = nullptr, *bOP = nullptr;
+  long b_items = 0;  // batched attention work items the partial buffers hold
   float2* bML = nullptr;
   u32x4 *bA = nullptr, *bOA = nullptr, *bHA = nullptr;  // fp16 A fragments of the GEMM inputs
   u32x4* bU = nullptr;     // fp16 A fragments of the fused rows of a batched append, per layer
@@ -684,7 +685,8 @@ int build(dflare_handle* h, const dflare_weights* w) {
     h->bpart_floats = part;
     TRY(dev_alloc(h, &h->bpart, (size_t)std::max(part, 64L) * 4));
     TRY(dev_zalloc(h, &h->bcnt, (size_t)kBCounters * 128));
-    const long items = (long)c.max_batch * ceil_div((long)c.max_context + B, kBKeys) * c.n_kv_heads;
+    const long items = std::max((long)c.max_batch * ceil_div((long)c.max_context + B, kBKeys) * c.n_kv_heads, 2L * h->cus);
+    h->b_items = items;
     TRY(dev_alloc(h, &h->bOP, (size_t)items * h->Rpad * hd * 4));
     TRY(dev_alloc(h, &h->bML, (size_t)items * h->Rpad * sizeof(float2)));
     // best (score, id) per group of output tiles and row (few-row calls: groups of 2 or 4 tiles)
@@ -1083,6 +1085,25 @@ int run_fuse_batched(dflare_handle* h, int n_seq, const int32_t* seq, const int3
   return DFLARE_OK;
 }
 
+// Keys per attention work item of a batched call and the items of its sequences (rows.keys, rows.ipfx).
+// An item takes kBKeys keys, as every further range of a sequence costs a pass over its partial
+// outputs, but half or a quarter of them while the call has fewer items than CUs (4 sequences of 301 ..
+// 3,000 rows, 8 KV heads x 128: attention 22 -> 16 us a layer, the merge 5 -> 6.6; twice as many items were
+// slower again: 8 sequences 1.91 against 1.84 ms).
+int attention_items(const dflare_handle* h, BRows& rows) {
+  const int B = h->cfg.block_size;
+  auto ranges = [&](int keys) {
+    long n = 0;
+    for (int i = 0; i < rows.n_seq; ++i) n += ceil_div(rows.L[i] + B, keys);
+    return n * h->cfg.n_kv_heads;
+  };
+  rows.keys = kBKeys;
+  while (rows.keys > kBKeysMin && ranges(rows.keys) < h->cus && ranges(rows.keys / 2) <= h->b_items) rows.keys /= 2;
+  for (int i = 0; i < rows.n_seq; ++i)
+    rows.ipfx[i + 1] = rows.ipfx[i] + ceil_div(rows.L[i] + B, rows.keys) * h->cfg.n_kv_heads;
+  return rows.ipfx[rows.n_seq];
+}
+
 int run_draft_batched(dflare_handle* h, int n_seq, const int32_t* seq, const int32_t* ids, int32_t* out) {
   const dflare_config& c = h->cfg;
   const int H = c.hidden, F = c.ffn, V = c.vocab, D = c.n_draft_layers, B = c.block_size, hd = c.head_dim;
@@ -1096,9 +1117,8 @@ int run_draft_batched(dflare_handle* h, int n_seq, const int32_t* seq, const int
     rows.seq[i] = seq[i];
     rows.L[i] = h->Ls[seq[i]];
     rows.off[i + 1] = (i + 1) * B;
-    rows.ipfx[i + 1] = rows.ipfx[i] + ceil_div(rows.L[i] + B, kBKeys) * c.n_kv_heads;
   }
-  const int items = rows.ipfx[n_seq];
+  const int items = attention_items(h, rows);
   BAttnArgs at{};
   at.Q = h->bQ;
   at.kc = h->kc;
