@@ -191,6 +191,21 @@ def test_batched_residual_parts():
     model.close()
 
 
+# attention items of 512, 256 and 128 keys (264 items of 512 with twelve sequences; eight and three
+# sequences have fewer than there are CUs), keys ending at a range, one past it and inside
+def test_batched_attention_ranges():
+    cfg = synth.ModelConfig("ranges", hidden=128, n_q_heads=8, n_kv_heads=8, head_dim=64, ffn=160, vocab=501,
+                            n_draft_layers=1, n_target_layers=2, block_size=16, context=1100)
+    slots = list(range(12))
+    print("[batched] attention ranges", flush=True)
+    lengths = [1100, 496, 1009, 1008, 1030, 1024, 1070, 1100, 1010, 1050, 1090, 1023]
+    model, orcs, _ = build_batched(cfg, lengths, slots, 12)
+    for n in (12, 8, 3):
+        _, _, worst = compare_draft(model, orcs, cfg, slots[:n])
+        print(f"[batched] attention ranges: {n} sequences, logits rel err {worst:.2e}", flush=True)
+    model.close()
+
+
 def test_batched_single_equals_batch1():
     """Slot 0 through the batch-1 calls, slot 1 through the batched calls, same rows."""
     cfg = CASES["hd128_b16"][0]
