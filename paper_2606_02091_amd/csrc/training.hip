@@ -547,9 +547,9 @@ __global__ __launch_bounds__(kTrT, KS == 1 ? 2 : 1) void k_aatt_rows(AttnT a) {
 // between the gradient products of the unit before, so that the exponentials have products beside
 // them; one wave per SIMD, with 512 registers.
 // Writes this chunk's partial dK, dV.  512 blocks, T = 3,072: 658 -> 500 us against 16-key waves with
-// transposed copies of Q and dO; with two waves per SIMD and 256 registers 650.  Work-groups start with the first key tiles, which
-// the most blocks see, so that the short ones fill the end (300 blocks of 8 x 16 rows, T = 3,072, 8 KV heads x
-// 64: 330 -> 284 us against chunk by chunk).
+// transposed copies of Q and dO; with two waves per SIMD and 256 registers 650.  Work-groups start
+// with the first key tiles, which the most blocks see, so that the short ones fill the end (300 blocks of
+// 8 x 16 rows, T = 3,072, 8 KV heads x 64: 330 -> 284 us against chunk by chunk).
 constexpr int kKvcKeys = 128;
 template <int HD>
 __global__ __launch_bounds__(kTrT, 1) void k_aatt_kvc(AttnT a) {
