@@ -19,6 +19,7 @@
 // for all of them before any LDS read that follows, so that a tile's products waited for the loads
 // just issued for the next (context dK, dV of 512 blocks, T = 3,072: 580 against 500 us).
 #include <hip/hip_runtime.h>
+#include <float.h>
 #include <math.h>
 
 #include <algorithm>
@@ -958,12 +959,13 @@ __global__ __launch_bounds__(kCeOT) void k_wce_chip(const float* logits, const i
 
 // The rows of a last, nearly empty turn of the kernel above, each cut into `pieces` for as many
 // work-groups: pass 0 leaves each piece's (max, sum of 2^(z log2 e - max)) in part, pass 1 forms the row's
-// from them in piece order and writes the gradient.  As above, rows without a weight give exact
-// zeros where `zero_off`.
+// from them in piece order and writes the gradient.  A piece of masked values alone (-inf, or so low
+// that the scaling overflows) leaves the sum 0 at the lowest finite maximum.  Rows without a loss get
+// zeros and are not read.
 template <int PASS>
 __global__ __launch_bounds__(kCeT) void k_wce_piece(const float* logits, const int32_t* labels, int row0, int pieces,
                                                     int V, int B, const float* w, const float* inv_wsum, float* part,
-                                                    float* ce_out, float* dz, bool zero_off) {
+                                                    float* ce_out, float* dz) {
   __shared__ float red[kCeT / 64];
   const int row = row0 + blockIdx.x / pieces, pc = blockIdx.x % pieces, tid = threadIdx.x;
   const float L2E = 1.4426950408889634f;
@@ -976,7 +978,7 @@ __global__ __launch_bounds__(kCeT) void k_wce_piece(const float* logits, const i
       const f32x4 x = z4[v];
       m = fmaxf(m, fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
     }
-    const float M = ce_reduce<kCeT, true>(m, red) * L2E;
+    const float M = fmaxf(ce_reduce<kCeT, true>(m, red) * L2E, -FLT_MAX);
     float sum = 0.f;
 #pragma unroll 4
     for (int v = v0 + tid; v < v1; v += kCeT) {
@@ -994,7 +996,7 @@ __global__ __launch_bounds__(kCeT) void k_wce_piece(const float* logits, const i
     float M = pp[0], S = pp[1];
     for (int k = 1; k < pieces; ++k) {
       const float nm = fmaxf(M, pp[2 * k]);
-      if (nm != -INFINITY) S = S * ex2(M - nm) + pp[2 * k + 1] * ex2(pp[2 * k] - nm);
+      S = S * ex2(M - nm) + pp[2 * k + 1] * ex2(pp[2 * k] - nm);
       M = nm;
     }
     const float lse2 = M + log2f(S);
@@ -1006,7 +1008,7 @@ __global__ __launch_bounds__(kCeT) void k_wce_piece(const float* logits, const i
 #pragma unroll 4
     for (int v = v0 + tid; v < v1; v += kCeT) {
       f32x4 o = zero4();
-      if (!(zero_off && c == 0.f)) {
+      if (c != 0.f) {
         const f32x4 x = z4[v];
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = c * ex2(fmaf(x[e], L2E, -lse2));
@@ -1263,9 +1265,9 @@ void launch_weighted_ce(hipStream_t st, const float* logits, const int32_t* labe
     if (tail > 0) {
       const int pieces = kCePieces / tail;
       hipLaunchKernelGGL((k_wce_piece<0>), dim3(tail * pieces), dim3(kCeT), 0, st, logits, labels, full, pieces, V, B,
-                         wr, inv, part, row_ce, dlogits, !chip);
+                         wr, inv, part, row_ce, dlogits);
       hipLaunchKernelGGL((k_wce_piece<1>), dim3(tail * pieces), dim3(kCeT), 0, st, logits, labels, full, pieces, V, B,
-                         wr, inv, part, row_ce, dlogits, !chip);
+                         wr, inv, part, row_ce, dlogits);
     }
   }
   hipLaunchKernelGGL(k_wce_loss, dim3(1), dim3(256), 0, st, wr, row_ce, rows, loss);

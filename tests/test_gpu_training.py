@@ -129,6 +129,43 @@ def test_weighted_ce_matches_oracle(V, n):
         dfl.weighted_ce(torch.from_numpy(z[:17]).cuda(), torch.from_numpy(y[:17]).cuda(), B, gamma)
 
 
+# a masked run of logits (-inf, or the lowest float) at the head, in the middle, at the tail, all but the last
+# five and all but the first value: longer than a piece, and than all a thread holds in registers; and a row
+# without a loss that is masked as a whole: exact zeros
+MASKS = ((0.0, 0.6), (0.3, 0.7), (0.55, 1.0), (0.0, -5), (1, 1.0))
+
+
+def masked_ce_case(V, n, low, B=16):
+    rng = np.random.default_rng(8)
+    z = (3.0 * rng.standard_normal((n * B, V))).astype(np.float32)
+    y = np.empty(n * B, np.int32)
+    for r in range(n * B):
+        lo, hi = MASKS[r % len(MASKS)]
+        lo = lo if isinstance(lo, int) else int(lo * V)
+        hi = V + hi if isinstance(hi, int) else int(hi * V)
+        z[r, lo:hi] = low
+        free = np.r_[0:lo, hi:V]
+        y[r] = free[rng.integers(0, free.size)]
+    z[0] = low
+    return z, y
+
+
+# rows held in registers, and a last turn in pieces (an on-chip vocabulary and a longer one)
+@pytest.mark.parametrize("low", [-np.inf, float(np.finfo(np.float32).min)])
+@pytest.mark.parametrize("V,n", [(1003, 3), (32003, 3), (98307, 1), (151936, 1), (201088, 1)])
+def test_weighted_ce_masked_logits(V, n, low):
+    print(f"[training] masked CE V={V} n={n} low={low}", flush=True)
+    z, y = masked_ce_case(V, n, low)
+    loss, ce, dz = (t.cpu().numpy() for t in dfl.weighted_ce(torch.from_numpy(z).cuda(), torch.from_numpy(y).cuda(),
+                                                             16, 4.5))
+    assert not dz[0].any() and ce[0] == 0.0
+    z[0] = 0.0  # (the oracle would form 0 x NaN)
+    rloss, rce, rdz = tr.weighted_ce(z.astype(np.float64), y, 16, 4.5)
+    assert abs(float(loss[0]) - rloss) <= 1e-5 * max(1.0, abs(rloss))
+    assert P.relinf(ce, rce) <= 1e-5
+    assert P.relinf(dz, rdz) <= 1e-5
+
+
 def test_anchor_attention_full_training_shape_sampled():
     """The training shape the benchmark times (T = 3,072, 512 blocks of B = 16, 32 query / 8 KV
     heads x 128): every kernel runs on the whole problem in its benchmark launch configuration
