@@ -818,7 +818,7 @@ __global__ __launch_bounds__(T) void k_wce_reg(const float* logits, const int32_
           rest *= ex2((m - mx) * L2E);
           m = mx;
         }
-        const float ml = m * L2E;
+        const float ml = fmaxf(m * L2E, -FLT_MAX);  // (finite while all values so far are masked: they add 0)
         rest += (exp4(x[0], ml) + exp4(x[1], ml)) + (exp4(x[2], ml) + exp4(x[3], ml));
       }
     }
