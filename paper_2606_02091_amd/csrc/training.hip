@@ -891,8 +891,9 @@ __global__ __launch_bounds__(kCeOT) void k_wce_chip(const float* logits, const i
     }
     const int nl = min(kCeOL, max(0, V4 - kCeOR * kCeOT));  // LDS pieces of this row
     // running (max, sum) of the log2-domain values, one 16-byte piece at a time (the register
-    // pieces in load order, so the sweep follows their arrival), then the LDS pieces
-    float m = -INFINITY, sum = 0.f;
+    // pieces in load order, so the sweep follows their arrival), then the LDS pieces; the maximum starts
+    // at the lowest finite value, so that masked values (-inf, or scaled to it) add 0
+    float m = -FLT_MAX, sum = 0.f;
     auto take4 = [&](f32x4 x) {
       const float t0 = x[0] * L2E, t1 = x[1] * L2E, t2 = x[2] * L2E, t3 = x[3] * L2E;
       const float m4 = fmaxf(fmaxf(t0, t1), fmaxf(t2, t3));
@@ -912,7 +913,7 @@ __global__ __launch_bounds__(kCeOT) void k_wce_chip(const float* logits, const i
     for (int off = 32; off > 0; off >>= 1) {
       const float om = __shfl_xor(m, off), os = __shfl_xor(sum, off);
       const float nm = fmaxf(m, om);
-      sum = (nm == -INFINITY) ? 0.f : sum * ex2(m - nm) + os * ex2(om - nm);
+      sum = sum * ex2(m - nm) + os * ex2(om - nm);
       m = nm;
     }
     if (lane == 0) {
@@ -933,12 +934,13 @@ __global__ __launch_bounds__(kCeOT) void k_wce_chip(const float* logits, const i
     const bool on = row % B > 0 && y >= 0 && y < V;
     if (tid == 0) ce_out[row] = on ? lse2 * 0.6931471805599453f - logits[(long)row * V + y] : 0.f;
     const float c = w[row] * inv;
-    // (c = 0 rows: c p = 0 for every value, so no branch per piece)
+    // (rows of weight 0: c 2^(x - inf) = 0 for every value, so no branch per piece)
+    const float sub = c == 0.f ? INFINITY : lse2;
     f32x4* d4 = reinterpret_cast<f32x4*>(dz + (long)row * V);
     auto grad = [&](f32x4 x, int v) {
       f32x4 o;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = c * ex2(fmaf(x[e], L2E, -lse2));
+      for (int e = 0; e < 4; ++e) o[e] = c * ex2(fmaf(x[e], L2E, -sub));
       __builtin_nontemporal_store(o, d4 + v);
     };
 #pragma unroll
@@ -950,7 +952,7 @@ __global__ __launch_bounds__(kCeOT) void k_wce_chip(const float* logits, const i
       const int y4 = y >> 2, rest = y4 - kCeOR * kCeOT;
       if ((rest < 0 ? y4 % kCeOT : rest % kCeOT) == tid) {
         const float zy = logits[(long)row * V + y];
-        dz[(long)row * V + y] = c * ex2(fmaf(zy, L2E, -lse2)) - c;
+        dz[(long)row * V + y] = c * ex2(fmaf(zy, L2E, -sub)) - c;
       }
     }
     __syncthreads();  // lrow is refilled by the next row

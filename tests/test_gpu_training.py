@@ -150,11 +150,11 @@ def masked_ce_case(V, n, low, B=16):
     return z, y
 
 
-# rows held in registers, their form with a rest (odd V, and V a multiple of 4), and a last turn in pieces (an
-# on-chip vocabulary and a longer one)
+# rows held in registers, their form with a rest (odd V, and V a multiple of 4), a last turn in pieces (an
+# on-chip vocabulary and a longer one), and rows held on chip (none in LDS, and the Qwen3 vocabulary)
 @pytest.mark.parametrize("low", [-np.inf, float(np.finfo(np.float32).min)])
 @pytest.mark.parametrize("V,n", [(1003, 3), (32003, 3), (98307, 1), (98309, 5), (201088, 5), (151936, 1),
-                                 (201088, 1)])
+                                 (201088, 1), (111616, 5), (151936, 5)])
 def test_weighted_ce_masked_logits(V, n, low):
     print(f"[training] masked CE V={V} n={n} low={low}", flush=True)
     z, y = masked_ce_case(V, n, low)
