@@ -719,6 +719,7 @@ __global__ void k_aatt_sum(const float* part, int nch, long n, float* dk, float*
 // flight at a time); last, the loss in row order. ----
 constexpr int kCeT = 1024;       // threads of the row work-group
 constexpr int kCeRows = 256;     // rows in flight (work-groups)
+constexpr int kCeLaunch = 1 << 21;  // most rows of one launch of a work-group per row (it takes less than 2^32 threads)
 constexpr int kCePieces = 512;   // work-groups of a last turn of rows cut into pieces
 constexpr int kCeTailMax = 64;   // rows of such a turn: from there both ways cost the same (151,936 values, 90 us)
 
@@ -771,10 +772,10 @@ __device__ __forceinline__ float ce_reduce(float v, float* red) {
 // 31 -> 19 us, 4,800 x 4,000 74 -> 37, 1,600 x 98,000 317 -> 246, 528 x 100,001 284 -> 96, 1,040 x 201,088
 // (with the last turn in pieces, below) 441 -> 357.
 template <int T, int S, bool REST>
-__global__ __launch_bounds__(T) void k_wce_reg(const float* logits, const int32_t* labels, int V, int B,
+__global__ __launch_bounds__(T) void k_wce_reg(const float* logits, const int32_t* labels, int row0, int V, int B,
                                                const float* w, const float* inv_wsum, float* ce_out, float* dz) {
   __shared__ float red[T / 64];
-  const int row = blockIdx.x, tid = threadIdx.x;
+  const int row = row0 + blockIdx.x, tid = threadIdx.x;
   const float L2E = 1.4426950408889634f;
   const float* z = logits + (long)row * V;
   float* d = dz + (long)row * V;
@@ -1243,7 +1244,9 @@ void launch_weighted_ce(hipStream_t st, const float* logits, const int32_t* labe
   float* part = w + rows + 64;
   hipLaunchKernelGGL(k_wce_weights, dim3(1), dim3(256), 0, st, labels, rows, V, B, gamma, w, w + rows);
   auto reg = [&](auto kernel, int n, int threads) {
-    hipLaunchKernelGGL(kernel, dim3(n), dim3(threads), 0, st, logits, labels, V, B, wr, inv, row_ce, dlogits);
+    for (int r0 = 0; r0 < n; r0 += std::min(n - r0, kCeLaunch))
+      hipLaunchKernelGGL(kernel, dim3(std::min(n - r0, kCeLaunch)), dim3(threads), 0, st, logits, labels, r0, V, B, wr,
+                         inv, row_ce, dlogits);
   };
   // rows that fit the registers of a work-group: the fewest threads that hold them, so that several
   // rows share a CU (300 x 16 rows of 4,000 values: 4 waves 37 us, 16 waves 74)

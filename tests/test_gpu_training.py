@@ -168,6 +168,28 @@ def test_weighted_ce_masked_logits(V, n, low):
     assert P.relinf(dz, rdz) <= 1e-5
 
 
+# more rows than one launch has work-groups for (2^32 threads)
+def test_weighted_ce_many_rows():
+    B, V, gamma = 16, 2, 4.5
+    rows = (1 << 24) + B
+    print(f"[training] CE of {rows} rows", flush=True)
+    z = torch.randn(rows, V, device="cuda", generator=torch.Generator("cuda").manual_seed(2))
+    y = torch.arange(rows, device="cuda", dtype=torch.int32) % 3 - 1
+    loss, ce, dz = dfl.weighted_ce(z, y, B, gamma)
+    b = torch.arange(rows, device="cuda") % B
+    w = torch.exp(-(b - 1).double() / gamma) * ((b > 0) & (y >= 0))
+    lse = torch.logsumexp(z.double(), dim=1)
+    want = torch.where(w > 0, lse - z.double().gather(1, y.clamp_min(0).long()[:, None])[:, 0], 0.0)
+    total = w.sum()
+    p = torch.exp(z.double() - lse[:, None])
+    p.scatter_add_(1, y.clamp_min(0).long()[:, None], -torch.ones_like(p[:, :1]))
+    p *= (w / total)[:, None]
+    rloss = (w * want).sum() / total
+    assert abs(float(loss) - float(rloss)) <= 1e-5 * max(1.0, abs(float(rloss)))
+    assert float((ce - want).abs().max()) <= 1e-5 * float(want.abs().max())
+    assert float((dz - p).abs().max()) <= 1e-5 * float(p.abs().max())
+
+
 def test_anchor_attention_full_training_shape_sampled():
     """The training shape the benchmark times (T = 3,072, 512 blocks of B = 16, 32 query / 8 KV
     heads x 128): every kernel runs on the whole problem in its benchmark launch configuration
