@@ -573,14 +573,17 @@ __global__ __launch_bounds__(kTrT, 1) void k_aatt_kvc(AttnT a) {
   const int nvis = __builtin_popcountll(__builtin_amdgcn_ballot_w64(myanc > key0));
   const int units = nvis * NPr;
 
+  // (a key that no block of the chunk sees takes part as zeros: its row may hold anything, NaN too)
   const int myk = key0 + 32 * w + n32;
+  const bool seen = myk < __builtin_amdgcn_readfirstlane(myanc);
   u32x4 kf[NK], vf[NK];
   {
+    const u32x4 z4 = {0u, 0u, 0u, 0u};
     const long row = ((long)min(myk, s.T - 1) * s.n_kv + g) * HD;
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
-      kf[k] = ld16(a.kc + row + k * 16 + 8 * h);
-      vf[k] = ld16(a.vc + row + k * 16 + 8 * h);
+      kf[k] = seen ? ld16(a.kc + row + k * 16 + 8 * h) : z4;
+      vf[k] = seen ? ld16(a.vc + row + k * 16 + 8 * h) : z4;
     }
   }
   f32x16 dk[ND], dv[ND];

@@ -105,6 +105,30 @@ def test_anchor_attention_kernel_forms(n, B, T, nq, nkv, hd):
         assert P.relinf(u.cpu().numpy(), v) <= P.REL_TOL, (nm, P.relinf(u.cpu().numpy(), v))
 
 
+# context rows past the last anchor (a buffer's unused end) may hold anything: no block reads them, their
+# gradients are zero, and the others are not touched.  Anchors at multiples of 64, the last inside a 128-key tile
+@pytest.mark.parametrize("hd", [64, 128])
+def test_anchor_attention_unused_context_rows(hd):
+    n, B, T, nq, nkv, top = 40, 16, 1152, 8, 2, 1088
+    print(f"[training] unused context rows hd={hd}", flush=True)
+    x, _, dout = inputs(n, B, T, nq, nkv, hd, seed=9)
+    anchors = (64 * np.random.default_rng(9).integers(0, top // 64 + 1, size=n)).astype(np.int32)
+    anchors[3] = top
+    x["k_ctx"][top:] = x["v_ctx"][top:] = 0  # as the oracle sees them
+    f64 = {k: synth.bf16_to_f32(v).astype(np.float64) for k, v in x.items()}
+    x["k_ctx"][top:] = x["v_ctx"][top:] = 0x7FC0  # NaN
+    d = {k: dev(v) for k, v in x.items()}
+    a = torch.from_numpy(anchors).cuda()
+    inp = (d["q"], d["k_ctx"], d["v_ctx"], d["k_blk"], d["v_blk"], a, B)
+    out, lse = dfl.anchor_attention_fwd(*inp)
+    got = (out, lse, *dfl.anchor_attention_bwd(*inp, out, lse, torch.from_numpy(dout.astype(np.float32)).cuda()))
+    want = (*tr.anchor_attention_fwd(**f64, anchors=list(anchors), B=B),
+            *tr.anchor_attention_bwd(**f64, anchors=list(anchors), B=B, dout=dout))
+    for nm, u, v in zip(("out", "lse", "dq", "dk_ctx", "dv_ctx", "dk_blk", "dv_blk"), got, want):
+        assert P.relinf(u.cpu().numpy(), v) <= P.REL_TOL, nm
+    assert not got[3][top:].any() and not got[4][top:].any()
+
+
 # (V, blocks): rows held in registers (up to 98,307 values: odd row starts, the last value of each
 # size), rows with a part past the registers (98,309; 152,516 and 201,088), and rows held on chip (V a
 # multiple of 4 in 111,616 .. 152,512): none in LDS, the Qwen3 vocabulary, LDS full; 17 blocks = 272
