@@ -678,8 +678,9 @@ __global__ __launch_bounds__(256, 2) void k_bstream(BGemmArgs g, BRows rows) {
       int bi[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        bi[e] = vc < g.V ? vc : 0x7FFFFFFF;
-        if (vc >= g.V) z[e] = -INFINITY;
+        const bool ok = vc < g.V && z[e] == z[e];  // a NaN score loses to every other
+        bi[e] = ok ? vc : 0x7FFFFFFF;
+        if (!ok) z[e] = -INFINITY;
       }
       row_best_to_lds(z, bi, col, s_bv[n] + r0, s_bi[n] + r0);
     }

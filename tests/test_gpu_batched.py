@@ -206,6 +206,40 @@ def test_batched_attention_ranges():
     model.close()
 
 
+# an LM-head row of NaN: its id loses to every finite score, in calls of few rows (the weight-streaming GEMM)
+# and of more (n = 11), greedy and sampled.  The row is the first of 16 output columns, in the tile and the group of
+# tiles of the token that the first block row gets without it
+def test_batched_nan_logit_loses():
+    cfg = synth.ModelConfig("nan", hidden=96, n_q_heads=4, n_kv_heads=2, head_dim=64, ffn=160, vocab=1001,
+                            n_draft_layers=1, n_target_layers=3, block_size=13, context=40, random_block=True)
+    w, lg = P.weights_for(cfg)
+    slots = list(range(11))
+    orcs = {s: P.oracle_for(cfg, w, lg, 64) for s in slots}
+    for s in slots:
+        orcs[s].append(slot_rows(cfg, s, 0, 5))
+    ids = np.stack([slot_ids(cfg, s) for s in slots])
+    clean = np.stack([np.array(orcs[s].draft_block(ids[i])["logits"]) for i, s in enumerate(slots)])
+    bad = sorted({int(t) // 64 * 64 for t in clean[0].argmax(-1)} | {int(t) // 16 * 16 for t in clean[0].argmax(-1)})
+    w["lm_head"] = w["lm_head"].copy()
+    w["lm_head"][bad] = 0x7FC0
+    clean[:, :, bad] = -np.inf
+    model = dfl.DraftModel(cfg, w, lg, max_context=64, max_new=16 * len(slots), max_batch=len(slots))
+    model.fuse_append_batched(slots, [5] * len(slots), dev(np.concatenate([slot_rows(cfg, s, 0, 5) for s in slots], axis=1)))
+    for n in (1, 2, 4, 5, 9, 11):
+        print(f"[batched] NaN logit: {n} sequences", flush=True)
+        tokens = model.draft_block_batched(slots[:n], ids_tensor(ids[:n])).cpu().numpy()
+        for i in range(n):
+            P.check_tokens(tokens[i], clean[i])
+        dfl.dflare_set_sampling(model.h, 0.8, 11)
+        drawn = model.draft_block_batched(slots[:n], ids_tensor(ids[:n])).cpu().numpy()
+        dfl.dflare_set_sampling(model.h, 0.0, 0)
+        for i, s in enumerate(slots[:n]):
+            _, scores = orc.sample_tokens(clean[i], 0.8, 11, 0, slot=s)
+            for b in range(cfg.block_size):
+                assert scores[b][drawn[i][b]] >= scores[b].max() - P.MARGIN, (n, s, b)
+    model.close()
+
+
 def test_batched_single_equals_batch1():
     """Slot 0 through the batch-1 calls, slot 1 through the batched calls, same rows."""
     cfg = CASES["hd128_b16"][0]
