@@ -408,6 +408,26 @@ void share_resid_width(GemmPlan& po, GemmPlan& pd, int Nt_o, int Kt_o, int Nt_d,
   }
 }
 
+// DFLARE_<WHAT>_<NAME>, the tuning override of a batched GEMM's choice: its value, 0 where it is not set
+int tuned(const char* what, const char* name) {
+  char key[64];
+  snprintf(key, sizeof key, "DFLARE_%s_%s", what, name);
+  const char* env = getenv(key);
+  return env ? atoi(env) : 0;
+}
+bool tuned_split(const char* name, int Kt, int* kg) {
+  const int v = tuned("BSPLIT", name);
+  if (v < 1 || v > kBSplitMax || v > Kt) return false;
+  *kg = v;
+  return true;
+}
+bool tuned_nw(const char* name, int* nw) {
+  const int v = tuned("BNW", name);
+  if (v != 3 && v != kBNW) return false;
+  *nw = v;
+  return true;
+}
+
 // K split of a batched GEMM (1 where the epilogue needs whole sums before it can start
 // or the tiles outnumber the arrival counters): the deepest split whose work-groups still
 // fit one per CU (tiles x kg <= CUs), each part keeping at least 8 k-tiles.  A sweep of the
@@ -421,12 +441,7 @@ int bgemm_split(int cus, const char* name, int Nt, int Mt, int Kt, int layers, b
   int best = 1;
   for (int kg : {2, 3, 4, 6, 8})
     if (tiles * kg <= cus && Kt >= 8 * kg) best = kg;
-  char key[64];
-  snprintf(key, sizeof key, "DFLARE_BSPLIT_%s", name);
-  if (const char* env = getenv(key)) {
-    const int v = atoi(env);
-    if (v >= 1 && v <= kBSplitMax && v <= Kt) best = v;
-  }
+  tuned_split(name, Kt, &best);
   return best;
 }
 
@@ -442,12 +457,7 @@ int bgemm_nw(int cus, const char* name, int Nt, int Mt, int Kt, int layers, bool
     return (double)wgs / (double)(((wgs + slots - 1) / slots) * slots);
   };
   int nw = allow && fill(3) > fill(kBNW) + 1e-9 ? 3 : kBNW;
-  char key[64];
-  snprintf(key, sizeof key, "DFLARE_BNW_%s", name);
-  if (const char* env = getenv(key)) {
-    const int v = atoi(env);
-    if (allow && (v == 3 || v == kBNW)) nw = v;
-  }
+  if (allow) tuned_nw(name, &nw);
   return nw;
 }
 
@@ -951,12 +961,15 @@ int ensure_f16_weights(dflare_handle* h) {
 //     (gate/up of 1,536 tiles at 64 rows 54 against 58 us; Q/K/V of 384 tiles 28 against 23).
 //   - More than four row tiles: only while two work-groups per CU hold the whole GEMM (Q/K/V of
 //     384 tiles at 128 rows 30 us, tiled 51; gate/up of 1,536 tiles 73, tiled 69).
+//   - A GEMM whose split or tile width is set by an override stays with the tiled kernel, which these describe.
 struct StreamShape {
   int tn, kg;
 };
-StreamShape bstream_shape(int cus, int epi, int Nt, int Mt, int Kt, int layers) {
+StreamShape bstream_shape(int cus, const char* name, int epi, int Nt, int Mt, int Kt, int layers) {
   StreamShape s{0, 1};
+  int v;
   if (Mt > kBStreamMt || epi == BEPI_BIAS16) return s;
+  if (epi != BEPI_ARGMAX && (tuned_split(name, Kt, &v) || tuned_nw(name, &v))) return s;
   if (epi == BEPI_RESID) {
     s.tn = Mt <= 4 ? 4 : 2;
     const long slots = Mt <= 4 ? cus : 2L * cus;
@@ -977,7 +990,7 @@ int bgemm(dflare_handle* h, int kind, const char* name, int epi, BGemmArgs& g, c
   g.zero = h->zero_tile;
   g.part = h->bpart;
   g.cnt = h->bcnt;
-  const StreamShape ss = bstream_shape(h->cus, epi, g.Nt, g.Mt, g.Kt, g.layers);
+  const StreamShape ss = bstream_shape(h->cus, name, epi, g.Nt, g.Mt, g.Kt, g.layers);
   prof_mark(h, kind, true);
   if (ss.tn) {
     g.nw = ss.tn;

@@ -240,6 +240,29 @@ def test_batched_nan_logit_loses():
     model.close()
 
 
+# the tuning overrides of the K split and the tile width act in calls of few rows too: another split adds in
+# another order, so the bits differ, and the result stays at the oracle
+def test_batched_overrides_act_in_small_calls(monkeypatch):
+    cfg = synth.ModelConfig("over", hidden=1056, n_q_heads=8, n_kv_heads=2, head_dim=128, ffn=2080, vocab=501,
+                            n_draft_layers=2, n_target_layers=3, block_size=13, context=40, random_block=True)
+    slots = [1, 0, 2]
+    got = {}
+    for name in ("", "QKV", "O", "DOWN"):
+        for kg in (1, 3) if name else (0,):
+            for k in ("QKV", "O", "DOWN"):  # the others without a split
+                monkeypatch.setenv(f"DFLARE_BSPLIT_{k}", str(kg) if k == name else "1")
+            if not name:
+                for k in ("QKV", "O", "DOWN"):
+                    monkeypatch.delenv(f"DFLARE_BSPLIT_{k}")
+            model, orcs, _ = build_batched(cfg, [40, 7, 16], slots, 3)
+            _, got[name, kg], worst = compare_draft(model, orcs, cfg, slots)
+            print(f"[batched] DFLARE_BSPLIT_{name}={kg}: logits rel err {worst:.2e}", flush=True)
+            model.close()
+    for name in ("QKV", "O", "DOWN"):
+        assert not np.array_equal(got[name, 1], got[name, 3]), name
+    assert np.array_equal(got["QKV", 1], got["O", 1]) and np.array_equal(got["QKV", 1], got["DOWN", 1])
+
+
 def test_batched_single_equals_batch1():
     """Slot 0 through the batch-1 calls, slot 1 through the batched calls, same rows."""
     cfg = CASES["hd128_b16"][0]
