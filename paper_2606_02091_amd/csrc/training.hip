@@ -1079,12 +1079,21 @@ struct WsLayout {
 };
 
 // Chunks of the context-key gradients: at most 64 blocks each (one per lane of a wave), and enough
-// of them that the (key tile, KV head, chunk) work-groups fill 256 CUs twice, down to 4 blocks.
+// of them that the (key tile, KV head, chunk) work-groups fill 256 CUs twice (kKvcGroups), down to 4 blocks.
+constexpr int kKvcGroups = 512;
+static int kv_chunks_least(const AttnShapeT& s) { return (s.n_blocks + kChunkBlocks - 1) / kChunkBlocks; }
+static int kv_chunks_most(const AttnShapeT& s) { return (s.n_blocks + 3) / 4; }
 static int kv_chunks(const AttnShapeT& s) {
-  const int least = (s.n_blocks + kChunkBlocks - 1) / kChunkBlocks, most = (s.n_blocks + 3) / 4;
   const long per = (long)((s.T + kKvcKeys - 1) / kKvcKeys) * s.n_kv;
-  const int fill = per > 0 ? (int)((512 + per - 1) / per) : 1;
-  return std::max(least, std::min(fill, most));
+  const int fill = per > 0 ? (int)((kKvcGroups + per - 1) / per) : 1;
+  return std::max(kv_chunks_least(s), std::min(fill, kv_chunks_most(s)));
+}
+// Rows of the chunks' partials that the workspace holds: at least kv_chunks(s) T n_kv (the chunks that fill the
+// chip are fewer than kKvcGroups / per + 1), and growing with every size, so that a workspace made for a
+// program's longest sequence and most blocks serves the smaller calls.
+static size_t kv_part_rows(const AttnShapeT& s) {
+  const size_t keys = (size_t)s.T * s.n_kv;
+  return std::max(kv_chunks_least(s) * keys, std::min(kv_chunks_most(s) * keys, (size_t)kKvcGroups * kKvcKeys + keys));
 }
 
 static WsLayout ws_layout(const AttnShapeT& s) {
@@ -1096,7 +1105,7 @@ static WsLayout ws_layout(const AttnShapeT& s) {
   L.st = o; o = al(o + padded * 8);
   L.qf = o; o = al(o + padded * s.hd * 2);
   L.df = o; o = al(o + padded * s.hd * 2);
-  L.part = o; o = al(o + (size_t)2 * L.nch * s.T * s.n_kv * s.hd * 4);
+  L.part = o; o = al(o + 2 * kv_part_rows(s) * s.hd * 4);
   L.order = o; o = al(o + (size_t)s.n_blocks * 4);
   L.total = o;
   return L;

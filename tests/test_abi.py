@@ -149,6 +149,19 @@ def test_anchor_attention_workspace_sizes(L):
         assert ws(*bad) == 0, bad
 
 
+# a workspace made for a program's longest sequence and most blocks serves the smaller calls, too
+@pytest.mark.parametrize("n_kv,G,hd", [(1, 1, 64), (1, 8, 128), (2, 4, 128), (8, 4, 128), (8, 8, 64)])
+def test_anchor_attention_workspace_grows_with_every_size(L, n_kv, G, hd):
+    ws = L.dflare_anchor_attention_workspace
+    blocks, lengths = (1, 4, 5, 16, 45, 64, 65, 200, 512, 1000), (0, 1, 127, 128, 777, 3072, 4224, 8320, 40000, 65536)
+    for B in (3, 16):
+        size = [[ws(n, B, T, n_kv * G, n_kv, hd) for T in lengths] for n in blocks]
+        for i, n in enumerate(blocks):
+            for j, T in enumerate(lengths):
+                assert i == 0 or size[i][j] >= size[i - 1][j], (n, T)
+                assert j == 0 or size[i][j] >= size[i][j - 1], (n, T)
+
+
 def test_anchor_attention_rejects_bad_arguments(L):
     p = ctypes.c_void_p(0x1000)  # never dereferenced: every case fails its checks first
     f = ctypes.cast(0x1000, ctypes.POINTER(ctypes.c_float))
