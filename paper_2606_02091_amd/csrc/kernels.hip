@@ -1994,14 +1994,24 @@ static void launch_kvt_rows(hipStream_t s, const KvtArgs& a, int layers, int mti
 }
 
 // Appends of up to 16 rows stream the weights through k_kvt (H = 2,560: 25 us, 26 with the
-// smallest tile of k_kvt_rows; H = 4,096: 35 and 36).  More rows take the smallest tile whose
-// work-groups all run at once, two per CU, else the largest: a larger tile re-reads less but runs
-// longer with idle CUs, and one more round of the smaller costs its whole length again
-// (H = 4,096, 32 x 64 / 32 x 128 / 64 x 128 / 128 x 128: 64 rows 39 / 43 / 61 / 95 us, 128 rows
-// 71 / 48 / 62 / 96, 256 rows 121 / 102 / 74 / 97, 512 rows 251 / 208 / 144 / 124).
+// smallest tile of k_kvt_rows; H = 4,096: 35 and 36), and so do more rows of a narrow projection of few
+// layers: k_kvt cuts K over the waves of a work-group, where a work-group of k_kvt_rows walks all of it, so
+// k_kvt is ahead while its work-groups all run at once, two per CU, and their re-reads of the weights
+// stay in the L2s (8 XCDs x 4 MB); with a short K the walk is short, and the line comes sooner (whole
+// append, k_kvt / k_kvt_rows: H = 4,096, 1 layer of 4 heads x 128, 64 rows 21 / 42 us, 256 rows (512 work-groups)
+// 44 / 51, 384 rows 64 / 56; H = 2,560, 1 layer of 8 heads, 64 rows 17 / 29, 192 rows (768) 37 / 31; H = 256, 2 layers
+// of 2 heads x 64, 64 rows 10.7 / 13.1, 256 rows (256) 12.5 / 12.0, 512 rows 16.0 / 12.5; H = 2,880, 8 layers of 8 heads
+// x 64 (46 MB), 32 rows (512) 37 / 35).
+// Otherwise the smallest tile whose work-groups all run at once, two per CU, else the largest: a larger
+// tile re-reads less but runs longer with idle CUs, and one more round of the smaller costs its whole
+// length again (H = 4,096, 32 x 64 / 32 x 128 / 64 x 128 / 128 x 128: 64 rows 39 / 43 / 61 / 95 us,
+// 128 rows 71 / 48 / 62 / 96, 256 rows 121 / 102 / 74 / 97, 512 rows 251 / 208 / 144 / 124).
 void launch_kvt(hipStream_t s, int cus, int nt_per_block, int waves, KvtArgs a, int layers, int mtiles) {
   a.kparts = waves;
-  if (mtiles > 1) {
+  const int ng = (a.Nt + nt_per_block - 1) / nt_per_block;
+  const long groups = (long)ng * layers * mtiles, weight_kb = (long)a.Nt * a.Kt * layers;
+  const bool stream = mtiles == 1 || (groups <= 2L * cus && 8 * groups <= (long)cus * a.Kt && weight_kb <= 32 * 1024);
+  if (!stream) {
     auto fits = [&](int rows, int cols) {
       return (long)((mtiles + rows - 1) / rows) * ((a.Nt + cols - 1) / cols) * layers <= 2L * cus;
     };
@@ -2011,7 +2021,7 @@ void launch_kvt(hipStream_t s, int cus, int nt_per_block, int waves, KvtArgs a, 
     else launch_kvt_rows<4, 4, 2, 2, 3>(s, a, layers, mtiles);
     return;
   }
-  const dim3 grid((a.Nt + nt_per_block - 1) / nt_per_block, layers, mtiles);
+  const dim3 grid(ng, layers, mtiles);
   if (nt_per_block == 2 && waves == 8) hipLaunchKernelGGL((k_kvt<2, 8>), grid, dim3(512), 0, s, a);
   else hipLaunchKernelGGL((k_kvt<1, 16>), grid, dim3(1024), 0, s, a);
 }
