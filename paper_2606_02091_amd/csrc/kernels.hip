@@ -138,10 +138,18 @@ __global__ __launch_bounds__(64) void k_fuse(const uint16_t* __restrict__ hidden
 // Bound by memory: the rows once and the fragments once.  The 16 rows of a tile run on one XCD,
 // whose L2 then fills whole lines of the fragments (16 bytes of a line per row): spread over the
 // XCDs, 512 rows took 51 us at H = 2,560, S = 18 and 60 at H = 2,880, S = 24, and here 37 and 39;
-// k_fuse takes 60 and 73 (H = 4,096, S = 36: 80 against 125).  With few rows its D-fold
-// parallelism wins (16 rows: 10 against 19 us); the two meet at 128 rows for all three shapes.
+// k_fuse takes 60 and 73 (H = 4,096, S = 36: 78 against 107).
 constexpr int kFuseMaxD = 8;
-constexpr int kFuseLayersRows = 128;  // rows of an append from which k_fuse_layers runs
+// Which of the two: a wave of k_fuse_layers walks the S rows in a chain, which k_fuse's D-fold number of waves,
+// with all their rows in flight, does not have.  The chain is hidden with enough waves per row of it, and the
+// fewer the layers, the less k_fuse reads again (8 layers, k_fuse / k_fuse_layers: H = 4,096, S = 36, 128 rows = 1,024
+// waves 35.7 / 34.8 us, 256 rows 60 / 42; H = 2,560, S = 36, 128 rows = 640 waves 26 / 32, 256 rows 41 / 36; H = 1,024,
+// S = 36, 256 rows = 512 waves 22 / 30; 4 layers: H = 4,096, S = 36, 128 rows 21 / 25, 208 rows 30 / 27; 2 layers:
+// H = 4,096, S = 18, 128 rows 12.8 / 14.2, 256 rows 21 / 18; 16 rows, H = 2,560, S = 18, 8 layers: 10 / 19).
+inline bool fuse_by_layers(int n, int S, int H, int D) {
+  const long waves = (long)n * ((H + 511) / 512);
+  return n >= 128 && D <= kFuseMaxD && waves >= 32L * S && D * waves >= 216L * S;
+}
 __global__ __launch_bounds__(64) void k_fuse_layers(const uint16_t* __restrict__ hidden, int ld, int S, int H, int n, int D,
                                                     const float* __restrict__ alpha, const float* __restrict__ gain,
                                                     float* ustats, u32x4* ua_hi, u32x4* ua_lo, int n_max, int mt_max) {
@@ -1935,7 +1943,7 @@ void launch_bf16_to_f32(hipStream_t s, float* dst, const uint16_t* src, long n) 
 void launch_fuse(hipStream_t s, const uint16_t* hidden, int n, int ld, int S, int H, int D, const float* alpha,
                  const float* gain, float* ustats, u32x4* ua_hi, u32x4* ua_lo, int n_max, int mt_max) {
   const int pairs = ((H + 511) / 512) * n;
-  if (n >= kFuseLayersRows && D <= kFuseMaxD) {
+  if (fuse_by_layers(n, S, H, D)) {
     const int tiles = ((n + 15) / 16) * ((H + 511) / 512);
     hipLaunchKernelGGL(k_fuse_layers, dim3((tiles + kXcds - 1) / kXcds * kXcds * 16), dim3(64), 0, s, hidden, ld, S,
                        H, n, D, alpha, gain, ustats, ua_hi, ua_lo, n_max, mt_max);

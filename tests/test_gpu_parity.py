@@ -182,8 +182,9 @@ def test_incremental_append_is_bitwise_bulk():
 # one append against appends of at most 16 rows, bit for bit: the many-row kernels at the edges of
 # their tiles (32, 64 and 128 rows; which tile runs follows from rows x heads x layers), ragged
 # rows, K ranges with fewer k-tiles than the K pieces (H = 96: three), a width that is no
-# multiple of the fusion's 512 columns, more layers than the fused kernel takes
-@pytest.mark.parametrize("hidden,n_kv,hd,layers", [(96, 8, 128, 8), (544, 16, 64, 8), (160, 3, 64, 9)])
+# multiple of the fusion's 512 columns, more layers than the fused kernel takes, and a projection so
+# narrow that the streaming kernel takes its many row tiles
+@pytest.mark.parametrize("hidden,n_kv,hd,layers", [(96, 8, 128, 8), (544, 16, 64, 8), (160, 3, 64, 9), (544, 1, 64, 2)])
 def test_many_row_append_is_bitwise_small_appends(hidden, n_kv, hd, layers):
     cfg = synth.ModelConfig("rows", hidden=hidden, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=hd, ffn=64, vocab=64,
                             n_draft_layers=layers, n_target_layers=7, block_size=4, context=520)
