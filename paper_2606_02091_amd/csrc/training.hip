@@ -37,8 +37,13 @@ constexpr int kTrT = 256;  // threads per work-group (4 waves)
 constexpr int kChunkBlocks = 64;  // most blocks per partial of the context-key gradients
 constexpr int kMaxBlockKeys = 16;  // block size B the training entry points accept
 // (block, KV head) pairs up to which a block's key tiles are split over a work-group's waves: above
-// one pair per CU the waves of further blocks occupy the chip without a merge (4 blocks of 64 rows, 8 KV
-// heads, T = 3,072: 48 us split, 79 us with 16-row waves)
+// one pair per CU the waves of further blocks occupy the chip without a merge.  Up to 256 pairs the split is ahead or
+// even in every form measured (forward, whole / split, heads of 128: 256 pairs of 32 rows, T = 3,072 74 / 49 us, T = 500
+// 19 / 16; of 64 rows 76 / 54 and 20 / 17; heads of 64, 32 rows 52 / 28 and 17 / 17).  Above, long contexts still favour it
+// (512 pairs of 32 rows, T = 3,072: 74 / 65) and short ones do not (T = 500: 384 pairs 20 / 23, 512 20 / 25), and from
+// 768 pairs neither does (73 / 86); anchors are not known to the host, so the line is where it never loses.  Blocks
+// of 65 to 128 rows occupy three or four waves themselves and are not split: their merge would need
+// work-groups of eight waves with twice the LDS.
 constexpr long kRowsSplitMax = 256;
 
 struct AttnShapeT {
@@ -1260,8 +1265,12 @@ void launch_weighted_ce(hipStream_t st, const float* logits, const int32_t* labe
       hipLaunchKernelGGL(kernel, dim3(std::min(n - r0, kCeLaunch)), dim3(threads), 0, st, logits, labels, r0, V, B, wr,
                          inv, row_ce, dlogits);
   };
-  // rows that fit the registers of a work-group: the fewest threads that hold them, so that several
-  // rows share a CU (300 x 16 rows of 4,000 values: 4 waves 37 us, 16 waves 74)
+  // rows that fit the registers of a work-group: the fewest registers that hold them, and the fewest threads,
+  // so that several rows share a CU.  4,096 rows with the form taken / with the next: 1,000 values 20 / 25 us, 4,000
+  // 32 / 34, 8,200 55 / 66, 16,400 96 / 103, 40,000 252 / 269, 58,000 376 / 391; at the upper end of a form the two are
+  // within 4% either way (24,000 152 / 148), and up to 240 rows within 1 us, except 512 threads against 1,024 at
+  // 49,000 values (16 rows 13.9 / 15.5).  From 65,536 to 81,920 values the form with a rest runs with an empty
+  // rest: 4 pieces a thread fewer than the form for 98,304 loads (16 rows of 65,540: 16.1 against 17.2).
   const int n4 = V / 4;
   if (n4 <= 512) reg(k_wce_reg<256, 2, false>, rows, 256);
   else if (n4 <= 2048) reg(k_wce_reg<256, 8, false>, rows, 256);
@@ -1269,6 +1278,7 @@ void launch_weighted_ce(hipStream_t st, const float* logits, const int32_t* labe
   else if (n4 <= 8192) reg(k_wce_reg<512, 16, false>, rows, 512);
   else if (n4 <= 12288) reg(k_wce_reg<512, 24, false>, rows, 512);
   else if (n4 <= 16384) reg(k_wce_reg<1024, 16, false>, rows, 1024);
+  else if (n4 <= 20480) reg(k_wce_reg<1024, 20, true>, rows, 1024);
   else if (n4 <= 24576) reg(k_wce_reg<1024, 24, false>, rows, 1024);
   else {
     // longer ones turn by turn of a row per CU, a nearly empty last turn cut into pieces

@@ -134,8 +134,8 @@ def test_anchor_attention_unused_context_rows(hd):
 # multiple of 4 in 111,616 .. 152,512): none in LDS, the Qwen3 vocabulary, LDS full; 17 blocks = 272
 # rows: a last turn of 16 rows cut into pieces, 23 = 368: one of 112 rows that is not
 @pytest.mark.parametrize("V,n", [(3, 2), (1000, 6), (1003, 6), (1000, 70), (2051, 3), (8195, 3), (16387, 3), (32003, 9),
-                                 (49155, 2), (65539, 2), (98307, 2), (98309, 2), (111616, 17), (111616, 23), (151936, 2),
-                                 (152512, 2), (152516, 17), (201088, 2)])
+                                 (49155, 2), (65539, 2), (65543, 2), (81923, 2), (81927, 2), (98307, 2), (98309, 2),
+                                 (111616, 17), (111616, 23), (151936, 2), (152512, 2), (152516, 17), (201088, 2)])
 def test_weighted_ce_matches_oracle(V, n):
     B = 16
     rng = np.random.default_rng(3)
