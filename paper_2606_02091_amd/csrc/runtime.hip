@@ -1001,6 +1001,8 @@ int bgemm(dflare_handle* h, int kind, const char* name, int epi, BGemmArgs& g, c
   } else {
     g.nw = bgemm_nw(h->cus, name, g.Nt, g.Mt, g.Kt, g.layers, epi != BEPI_ARGMAX && epi != BEPI_BIAS16);
     g.kg = bgemm_split(h->cus, name, g.Nt, g.Mt, g.Kt, g.layers, epi != BEPI_ARGMAX, g.nw);
+    // (an override set after the handle was made may ask for more parts than its partial area holds)
+    if ((long)bgemm_groups(g.Nt, g.Mt, g.nw) * g.layers * g.kg * kBPartFloats > h->bpart_floats) g.kg = 1;
     g.pld = h->b_mt * 16;
     g.n_groups = ceil_div(g.Nt, kBWaves * g.nw);
     launch_bgemm(h->stream, epi, g, rows);

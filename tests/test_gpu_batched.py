@@ -263,6 +263,19 @@ def test_batched_overrides_act_in_small_calls(monkeypatch):
     assert np.array_equal(got["QKV", 1], got["O", 1]) and np.array_equal(got["QKV", 1], got["DOWN", 1])
 
 
+# an override set after the handle was made cannot ask for more than its partial area holds
+def test_batched_override_after_init_stays_in_bounds(monkeypatch):
+    cfg = synth.ModelConfig("late", hidden=1056, n_q_heads=8, n_kv_heads=2, head_dim=128, ffn=2080, vocab=501,
+                            n_draft_layers=2, n_target_layers=3, block_size=13, context=40, random_block=True)
+    slots = [1, 0, 2]
+    print("[batched] late override", flush=True)
+    model, orcs, _ = build_batched(cfg, [40, 7, 16], slots, 3)
+    for name in ("QKV", "O", "GU", "DOWN"):
+        monkeypatch.setenv(f"DFLARE_BSPLIT_{name}", "8")
+    compare_draft(model, orcs, cfg, slots)
+    model.close()
+
+
 def test_batched_single_equals_batch1():
     """Slot 0 through the batch-1 calls, slot 1 through the batched calls, same rows."""
     cfg = CASES["hd128_b16"][0]
