@@ -153,10 +153,13 @@ def test_batched_matches_oracles(name):
 
 # calls of one to eight row tiles (the weight-streaming GEMM picks its shape by them), ragged rows
 # (B = 13); k-tiles per wave from none (H = 96: three k-tiles for four waves) to several, residual
-# projections with and without a K split (q = 1,024, F = 2,080), greedy and sampled
-@pytest.mark.parametrize("hidden,n_q,n_kv,hd,ffn", [(96, 4, 2, 64, 160), (1056, 8, 2, 128, 2080)])
-def test_batched_few_rows(hidden, n_q, n_kv, hd, ffn):
-    cfg = synth.ModelConfig("few", hidden=hidden, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=hd, ffn=ffn, vocab=1001,
+# projections with and without a K split (q = 1,024, F = 2,080), four output tiles per work-group for
+# three and four row tiles (Q/K/V, gate/up and LM head of more than 1,020 output tiles; 1,027 in the LM
+# head, so that its last work-group has three), greedy and sampled
+@pytest.mark.parametrize("hidden,n_q,n_kv,hd,ffn,vocab", [(96, 4, 2, 64, 160, 1001), (1056, 8, 2, 128, 2080, 1001),
+                                                          (160, 64, 32, 128, 8224, 16421)])
+def test_batched_few_rows(hidden, n_q, n_kv, hd, ffn, vocab):
+    cfg = synth.ModelConfig("few", hidden=hidden, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=hd, ffn=ffn, vocab=vocab,
                             n_draft_layers=2, n_target_layers=3, block_size=13, context=40, random_block=True)
     slots = [5, 0, 3, 9, 1, 7, 2, 8, 4]
     print(f"[batched] few rows H={hidden}", flush=True)

@@ -87,6 +87,7 @@ def test_anchor_attention_matches_oracle(name):
     (5, 16, 129, 4, 1, 64), (261, 11, 65, 4, 1, 128), (129, 16, 127, 8, 2, 64),   # two
     (9, 11, 128, 8, 1, 64), (33, 16, 160, 6, 1, 128),                             # three
     (7, 16, 257, 8, 1, 128), (70, 13, 96, 16, 2, 64),                             # four
+    (130, 1, 4096, 16, 16, 64), (128, 1, 4096, 16, 16, 64),  # context gradients in chunks of 44 and of 64 blocks
 ])
 def test_anchor_attention_kernel_forms(n, B, T, nq, nkv, hd):
     print(f"[training] attention form {(n, B, T, nq, nkv, hd)}", flush=True)
@@ -190,6 +191,25 @@ def test_weighted_ce_masked_logits(V, n, low):
     assert abs(float(loss[0]) - rloss) <= 1e-5 * max(1.0, abs(rloss))
     assert P.relinf(ce, rce) <= 1e-5
     assert P.relinf(dz, rdz) <= 1e-5
+
+
+# gradients aligned otherwise than the logits: rows held in registers and their form with a rest
+@pytest.mark.parametrize("V", [1003, 32004, 98309, 201088])
+def test_weighted_ce_gradient_alignment(V):
+    B, rows = 16, 80
+    print(f"[training] CE gradient alignment V={V}", flush=True)
+    g = torch.Generator("cuda").manual_seed(4)
+    z = torch.randn(rows, V, device="cuda", generator=g)
+    y = torch.randint(0, V, (rows,), device="cuda", dtype=torch.int32, generator=g)
+    want = dfl.weighted_ce(z, y, B, 4.5)
+    for shift in (1, 2, 3):
+        buf = torch.full((rows * V + 8,), 7.0, device="cuda")
+        loss, ce = torch.empty(1, device="cuda"), torch.empty(rows, device="cuda")
+        dz = buf[shift:shift + rows * V]
+        dfl.weighted_ce_noalloc(z, y, B, 4.5, loss, ce, dz)
+        torch.cuda.synchronize()
+        assert torch.equal(loss, want[0]) and torch.equal(ce, want[1]) and torch.equal(dz.view(rows, V), want[2])
+        assert (buf[:shift] == 7.0).all() and (buf[shift + rows * V:] == 7.0).all()
 
 
 # more rows than one launch has work-groups for (2^32 threads)

@@ -127,3 +127,24 @@ def test_variant_batched(vname):
     _, _, worst = TB.compare_draft(model, orcs, cfg, slots)
     print(f"[variant] {vname} batched: logits rel err {worst:.2e}", flush=True)
     model.close()
+
+
+# the context projection of many rows with +FC's bias: tiled (8 layers of 8 heads) and streamed (one head),
+# bit for bit as appends of at most 16 rows give it
+@pytest.mark.parametrize("n_kv,layers", [(8, 8), (1, 2)])
+def test_post_fc_many_row_append_is_bitwise_small_appends(n_kv, layers):
+    cfg = synth.ModelConfig("fcrows", hidden=192, n_q_heads=n_kv, n_kv_heads=n_kv, head_dim=64, ffn=64, vocab=64,
+                            n_draft_layers=layers, n_target_layers=5, block_size=4, context=150)
+    print(f"[variant] post_fc many rows n_kv={n_kv} D={layers}", flush=True)
+    w, lg = weights(cfg)
+    rows = synth.hidden_rows(cfg, 0, 150)
+    caches = []
+    for step in (15, 150):
+        model = dfl.DraftModel(cfg, w, lg, max_context=160, max_new=150, variant=dfl.VARIANT_POST_FC)
+        for s in range(0, 150, step):
+            model.fuse_append(TP.dev(np.ascontiguousarray(rows[:, s:s + step])))
+        caches.append([dfl.dflare_debug_read(model.h, what, i, (150, n_kv, 64)) for i in range(layers)
+                       for what in (dfl.DBG_KCACHE, dfl.DBG_VCACHE)])
+        model.close()
+    for a, b in zip(*caches):
+        assert a.any() and np.array_equal(a, b)
