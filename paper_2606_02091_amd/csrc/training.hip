@@ -708,10 +708,12 @@ __global__ __launch_bounds__(kTrT, 1) void k_aatt_kvc(AttnT a) {
   }
 }
 
-// context dK, dV = the chunks' partials added in chunk order
+// context dK, dV = the chunks' partials added in chunk order (eight loads of each in flight: with few keys
+// and many blocks one thread's chain of chunks is what the kernel takes)
 __global__ void k_aatt_sum(const float* part, int nch, long n, float* dk, float* dv) {
   for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < n; e += (long)gridDim.x * blockDim.x) {
     float sk = 0.f, sv = 0.f;
+#pragma unroll 8
     for (int c = 0; c < nch; ++c) {
       sk += part[(long)c * n + e];
       sv += part[((long)nch + c) * n + e];
