@@ -254,7 +254,12 @@ int dflare_context_len(const dflare_handle* h, int32_t* out);
  *   n_seq          1 <= n_seq <= max_batch
  *   seq            HOST int32 [n_seq]: distinct slots in [0, max_batch)
  * Results are those of the batch-1 calls on each slot in turn, up to rounding
- * order: the batched kernels sum in a different order (same precision).
+ * order: the batched kernels sum in a different order (same precision).  The order is a
+ * function of the call -- the number of its rows chooses the GEMM kernels, the lengths of all
+ * its sequences the ranges of keys the attention is cut into -- so the same call repeats bit
+ * for bit, while a sequence's logits differ by rounding (about 1e-3 of their size at the
+ * larger model shapes, under half the error against exact arithmetic) between calls with
+ * other neighbours.
  */
 
 /*
@@ -458,7 +463,9 @@ int dflare_read_probe(const void* buf, int64_t bytes, uint32_t* sink, void* stre
  *   out            DEVICE fp32 [n_blocks*B, n_q, hd];  lse  DEVICE fp32 [n_blocks*B, n_q]
  *                  (natural log-sum-exp of each row's scaled scores, for the backward pass)
  *   workspace      DEVICE scratch of at least dflare_anchor_attention_workspace(...) bytes
- *                  (operand copies and partial sums; contents need not be kept)
+ *                  (operand copies and partial sums; contents need not be kept).  The size grows with
+ *                  n_blocks, B and T, so one workspace for the largest call serves the smaller ones.
+ * Context rows from the largest anchor on are seen by no block and have zero gradients.
  * Supported: 1 <= B <= 16, hd 64 or 128, (n_q / n_kv) * B <= 128; else UNSUPPORTED.  The
  * products run on bf16 matrix cores (probabilities and gradients rounded to bf16 as operands,
  * fp32 accumulation).  Asynchronous on `stream` (hipStream_t, NULL = default).  Gradients are
@@ -484,14 +491,15 @@ int dflare_anchor_attention_bwd(const void* q, const void* k_ctx, const void* v_
 /*
  * Progressive position-weighted cross-entropy (Sec. 4.3, Eq. 5) over rows = n_blocks * B
  * block positions: row r is position b = r % B of its block; the anchor position (b = 0)
- * and rows with label < 0 (or >= V) carry no loss; position b >= 1 has weight
+ * and rows with label < 0 (or >= V) carry no loss and get zeros; position b >= 1 has weight
  * w = exp(-(b - 1) / gamma), gamma = gamma(s) of the schedule (the caller's).  The loss is
  * sum w CE / sum w.
  *   logits   DEVICE fp32 [rows, V];  labels  DEVICE int32 [rows]
  *   loss     DEVICE fp32 [1] out;  row_ce  DEVICE fp32 [rows] out (CE per row, 0 where no loss)
  *   dlogits  DEVICE fp32 [rows, V] out: d loss / d logits
  *   workspace DEVICE scratch of at least dflare_weighted_ce_workspace(rows) bytes
- * rows not a multiple of B, gamma <= 0 or not finite: INVALID_ARG.  Deterministic.
+ * rows not a multiple of B, gamma <= 0 or not finite: INVALID_ARG.  Deterministic.  Logits may be
+ * masked with -inf (or the lowest float), as long as a row with a loss keeps one that is not.
  */
 size_t dflare_weighted_ce_workspace(int32_t rows);
 int dflare_weighted_ce(const float* logits, const int32_t* labels, int32_t rows, int32_t V, int32_t B, float gamma,
@@ -502,15 +510,15 @@ int dflare_weighted_ce(const float* logits, const int32_t* labels, int32_t rows,
  * dflare_weighted_ce_noalloc -- the weighted CE above for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc).  Same arguments, results and kernels as dflare_weighted_ce, without the
- * workspace: the row weights and 1 / sum w live in a fixed device array of the library
- * (DFLARE_WEIGHTED_CE_NOALLOC_MAX_ROWS + 64 floats, 256 KiB + 256 B; each GPU the library
- * runs on holds its own copy until the process ends).  Calls no hipMalloc, hipFree or other
- * allocating routine.  rows > DFLARE_WEIGHTED_CE_NOALLOC_MAX_ROWS: INVALID_ARG; a non-NULL
- * `stream` must belong to the current device (else INVALID_ARG).  The array is shared by
- * every call on a GPU and keeps the last call's contents (each call writes every value it
- * reads before reading it): calls that overlap in time on one GPU (different streams, or
- * different host threads) race and give undefined results; calls ordered on one stream do
- * not.
+ * workspace: the row weights, 1 / sum w and the partial sums of rows cut into pieces live in a
+ * fixed device array of the library (DFLARE_WEIGHTED_CE_NOALLOC_MAX_ROWS + 64 + 1,024 floats,
+ * 260 KiB + 256 B; each GPU the library runs on holds its own copy until the process ends).
+ * Calls no hipMalloc, hipFree or other allocating routine.
+ * rows > DFLARE_WEIGHTED_CE_NOALLOC_MAX_ROWS: INVALID_ARG; a non-NULL `stream` must belong to
+ * the current device (else INVALID_ARG).  The array is shared by every call on a GPU and keeps
+ * the last call's contents (each call writes every value it reads before reading it): calls
+ * that overlap in time on one GPU (different streams, or different host threads) race and give
+ * undefined results; calls ordered on one stream do not.
  */
 #define DFLARE_WEIGHTED_CE_NOALLOC_MAX_ROWS 65536
 int dflare_weighted_ce_noalloc(const float* logits, const int32_t* labels, int32_t rows, int32_t V, int32_t B,

@@ -48,7 +48,7 @@ struct BGemmArgs {
   int Nt, Kt, Mt, M, kg, layers;
   int nw;              // n-tiles per wave: kBNW, or 3 where that fills the CUs better (few rows: per work-group)
   const u32x4* zero;   // one zero fragment
-  float* part;         // partial tiles [tiles][kg][kBPartFloats]
+  float* part;         // partial tiles [tiles][kg][kBPartFloats]; RESID: rows [kg][Mt * 16][H]
   unsigned* cnt;       // arrival counters [tiles], 32 words apart, zero between launches
   // QKV (block rows) and KVT (appended context rows): queries [Mt * 16, q_dim] fp32; keys and
   // values (fp16) to the rows' sequence caches at their slots; RoPE at the slot position

@@ -281,7 +281,8 @@ __device__ __forceinline__ void kvt_store(const KvtArgs& a, int layer, int nt, i
 // ------------------------------------------------------------------------------------------
 // context K/V projection of fuse_append (Eq. 4, W^t): RoPE(f W_K^t) and f W_V^t for every
 // appended row of every draft layer, into cache slots L + row.  Weight-streaming GEMM:
-// block (group of NT output tiles, layer, 16-row m-tile); its WAVES waves split the k range
+// block (group of NT output tiles, layer, 16-row m-tile: one, or the several of a narrow
+// projection, see launch_kvt); its WAVES waves split the k range
 // and add their partial sums in LDS in wave order.  Two register sets alternate so that one
 // batch of loads is in flight while the previous one goes through the matrix cores.
 // ------------------------------------------------------------------------------------------
@@ -408,7 +409,8 @@ __global__ __launch_bounds__(64 * WAVES) void k_kvt(KvtArgs a) {
 // The same projection for appends of many rows (prompt ingestion).  k_kvt streams the whole
 // weight matrix once per 16 rows; here a work-group of 4 waves (WM x WN) owns WM MT row tiles x
 // WN NT output tiles, and each k-tile's fragments (both A planes and the weights) go through a
-// three-stage LDS ring filled by LDS-direct loads two k-tiles ahead, one barrier per k-tile.
+// LDS ring of NS stages (three to six, as the LDS allows) filled by LDS-direct loads NS - 1 k-tiles
+// ahead, one barrier per k-tile.
 // The K range is cut into the same a.kparts pieces that k_kvt's waves take, each accumulated
 // from zero and added in order, so that every row's result is the one k_kvt gives bit for bit,
 // however many rows an append holds.  Bound by the barrier and LDS latency of a k-tile (two
@@ -514,7 +516,7 @@ __global__ __launch_bounds__(256, 2) void k_kvt_rows(KvtArgs a) {
 #pragma unroll
       for (int n = 0; n < NT; ++n) ah[m][n] = al[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (; kt < end; ++kt) {
-      // this wave's loads of k-tile kt have landed (those of kt + 1 may be in flight), then
+      // this wave's loads of k-tile kt have landed (those of the later ones may be in flight), then
       // everybody's; every wave is past its reads of k-tile kt - 1, whose buffer is refilled
       if (kt + NS - 2 < a.Kt) wait_vm_barrier<(NS - 2) * PER>();
       else wait_vm_barrier<0>();

@@ -724,9 +724,9 @@ __global__ void k_aatt_sum(const float* part, int nch, long n, float* dk, float*
 }
 
 // ---- weighted CE (Eq. 5).  The row weights and 1 / sum w depend on labels and block positions
-// only and come first; then each row's log-sum-exp, CE and gradient in one work-group pass over
-// the row twice (the second read finds the row in the memory-side cache: gridDim.x rows are in
-// flight at a time); last, the loss in row order. ----
+// only and come first; then each row's log-sum-exp, CE and gradient, a work-group per row: held in
+// registers as a whole or in part (k_wce_reg), held on chip (k_wce_chip), or cut into pieces for
+// several work-groups (k_wce_piece); last, the loss in row order. ----
 constexpr int kCeT = 1024;       // threads of the row work-group
 constexpr int kCeRows = 256;     // rows in flight (work-groups)
 constexpr int kCeLaunch = 1 << 21;  // most rows of one launch of a work-group per row (it takes less than 2^32 threads)
@@ -1308,7 +1308,8 @@ bool ce_args_ok(const float* logits, const int32_t* labels, int32_t rows, int32_
          gamma > 0.f && isfinite(gamma);
 }
 
-// Scratch of the allocation-free weighted CE: the row weights and 1 / sum w of one call.
+// Scratch of the allocation-free weighted CE: the row weights, 1 / sum w and the pieces' partial
+// sums of one call.
 // Each GPU the library runs on holds its own copy until the process ends.  In host code the
 // array's name is not a device address: kernels get the address hipGetSymbolAddress returns
 // for the current device, looked up once per device.
