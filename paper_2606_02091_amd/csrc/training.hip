@@ -708,15 +708,25 @@ __global__ __launch_bounds__(kTrT, 1) void k_aatt_kvc(AttnT a) {
   }
 }
 
-// context dK, dV = the chunks' partials added in chunk order (eight loads of each in flight: with few keys
-// and many blocks one thread's chain of chunks is what the kernel takes)
+// context dK, dV = the chunks' partials added in chunk order, U of each loaded at a time
+template <int U>
 __global__ void k_aatt_sum(const float* part, int nch, long n, float* dk, float* dv) {
   for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < n; e += (long)gridDim.x * blockDim.x) {
     float sk = 0.f, sv = 0.f;
-#pragma unroll 8
-    for (int c = 0; c < nch; ++c) {
-      sk += part[(long)c * n + e];
-      sv += part[((long)nch + c) * n + e];
+    for (int c0 = 0; c0 < nch; c0 += U) {
+      float xk[U], xv[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {  // (past the last chunk the last again)
+        const long c = min(c0 + u, nch - 1);
+        xk[u] = part[c * n + e];
+        xv[u] = part[(nch + c) * n + e];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c0 + u < nch) {
+          sk += xk[u];
+          sv += xv[u];
+        }
     }
     dk[e] = sk;
     dv[e] = sv;
@@ -1241,9 +1251,12 @@ int dflare_anchor_attention_bwd(const void* q, const void* k_ctx, const void* v_
       hipLaunchKernelGGL((k_aatt_kvc<HD>), dim3((T + kKvcKeys - 1) / kKvcKeys * n_kv * a.nch), dim3(kTrT), 0, st, a);
     });
   if (T > 0) {
+    // few keys and many blocks: a thread's chain of chunks is what the sum takes (256 values, 250 chunks: 54 us with
+    // one load at a time, 10 with eight); with more values the waves hide it and the repeats of the last chunk
+    // cost (397,824 values, 11 chunks: 6.3 us against 7.6)
     const long n = (long)T * n_kv * hd;
-    hipLaunchKernelGGL(k_aatt_sum, dim3((int)std::min<long>((n + 255) / 256, 4096)), dim3(256), 0, st, a.part, a.nch,
-                       n, dk_ctx, dv_ctx);
+    hipLaunchKernelGGL(n < 65536 ? k_aatt_sum<8> : k_aatt_sum<1>, dim3((int)std::min<long>((n + 255) / 256, 4096)),
+                       dim3(256), 0, st, a.part, a.nch, n, dk_ctx, dv_ctx);
   }
   return hipGetLastError() == hipSuccess ? DFLARE_OK : DFLARE_ERR_HIP;
 }
