@@ -181,9 +181,11 @@ def test_batched_few_rows(hidden, n_q, n_kv, hd, ffn, vocab):
 
 # calls of nine and ten row tiles on the tiled GEMM, whose residual projections leave their K parts to
 # the norm: a second group of row tiles that is not full, a last column group that is not (66
-# output tiles), parts of unequal length (33 and 65 k-tiles), ragged rows (B = 13)
-def test_batched_residual_parts():
-    cfg = synth.ModelConfig("parts", hidden=1056, n_q_heads=8, n_kv_heads=2, head_dim=128, ffn=2080, vocab=501,
+# output tiles), parts of unequal length (33 and 65 k-tiles), ragged rows (B = 13); and projections too
+# short for a split (8 and 5 k-tiles), which add to the residual stream themselves
+@pytest.mark.parametrize("hidden,n_q,hd,ffn", [(1056, 8, 128, 2080), (96, 4, 64, 160)])
+def test_batched_residual_parts(hidden, n_q, hd, ffn):
+    cfg = synth.ModelConfig("parts", hidden=hidden, n_q_heads=n_q, n_kv_heads=2, head_dim=hd, ffn=ffn, vocab=501,
                             n_draft_layers=2, n_target_layers=3, block_size=13, context=40, random_block=True)
     slots = [5, 0, 3, 9, 1, 7, 2, 8, 4, 11, 6, 10]
     print("[batched] residual parts", flush=True)
