@@ -499,7 +499,8 @@ int dflare_anchor_attention_bwd(const void* q, const void* k_ctx, const void* v_
  *   dlogits  DEVICE fp32 [rows, V] out: d loss / d logits
  *   workspace DEVICE scratch of at least dflare_weighted_ce_workspace(rows) bytes
  * rows not a multiple of B, gamma <= 0 or not finite: INVALID_ARG.  Deterministic.  Logits may be
- * masked with -inf (or the lowest float), as long as a row with a loss keeps one that is not.
+ * masked with -inf (or the lowest float), as long as a row with a loss keeps one that is not; NaN
+ * and +inf make the results of their row NaN where it has a loss, and may do so where it has none.
  */
 size_t dflare_weighted_ce_workspace(int32_t rows);
 int dflare_weighted_ce(const float* logits, const int32_t* labels, int32_t rows, int32_t V, int32_t B, float gamma,
